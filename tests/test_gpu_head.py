@@ -107,3 +107,21 @@ def test_head_deterministic(orc):
     b = _gpu(d, 50)
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("V", [1, 3, 5, 1023, 1025, 64512, 64513, 130001])
+def test_vocab_compaction_edges(V):
+    """The marks' compaction over 63 ranges of whole 1024s: one mark, ranges
+    that end inside a vector, empty ranges, first and last token."""
+    _announce(f"vocab compaction V={V}")
+    g = torch.Generator().manual_seed(V)
+    T, k = 40, min(V, 50)
+    table = torch.randint(0, V, (V, k), generator=g, dtype=torch.int32)
+    targets = torch.randint(0, V, (T,), generator=g, dtype=torch.int32)
+    targets[0], targets[1] = 0, V - 1
+    table[:, 0] = torch.arange(V, dtype=torch.int32)
+    rows = torch.arange(T, dtype=torch.int32)
+    J, tpos = lm.lm_head_build_vocab(table.cuda(), k, targets.cuda(), rows.cuda())
+    want = torch.unique(table[targets.long()])
+    assert torch.equal(J.cpu(), want)
+    assert torch.equal(want[tpos.cpu().long()], targets)
