@@ -129,8 +129,8 @@ lora_status_t lora_ckpt_forward(const lora_node_t *nodes, int n, int64_t T, cons
     // the node's input leaves for the host as soon as it exists
     if ((e = hipEventRecord(produced[i], cs)) != hipSuccess) return hipfail(e, "event");
     if ((e = hipStreamWaitEvent(xs, produced[i], 0)) != hipSuccess) return hipfail(e, "wait");
-    if ((e = hipMemcpyAsync((char *)host_stash + p.stash_off[i], cur, (size_t)T * nd.d_in * 2,
-                            hipMemcpyDeviceToHost, xs)) != hipSuccess)
+    if ((e = lora::launch_host_copy((char *)host_stash + p.stash_off[i], cur, (size_t)T * nd.d_in * 2, true, xs)) !=
+        hipSuccess)
       return hipfail(e, "copy to host");
     if ((e = hipEventRecord(copied[i], xs)) != hipSuccess) return hipfail(e, "event");
     // output buffer: the caller's for the last node, else the one that held
@@ -172,8 +172,8 @@ lora_status_t lora_ckpt_backward(const lora_node_t *nodes, int n, int64_t T, con
     // buffer act[i % 2] last held the input of node i + 2
     hipError_t r;
     if (i + 2 < n && (r = hipStreamWaitEvent(xs, done[i + 2], 0)) != hipSuccess) return r;
-    if ((r = hipMemcpyAsync(act[i % 2], (const char *)host_stash + p.stash_off[i],
-                            (size_t)T * nodes[i].d_in * 2, hipMemcpyHostToDevice, xs)) != hipSuccess)
+    if ((r = lora::launch_host_copy(act[i % 2], (const char *)host_stash + p.stash_off[i],
+                                    (size_t)T * nodes[i].d_in * 2, false, xs)) != hipSuccess)
       return r;
     return hipEventRecord(loaded[i], xs);
   };

@@ -178,6 +178,11 @@ hipError_t launch_fill_nan(float *p, int64_t n, hipStream_t st);
 hipError_t launch_dh_finish(const float *acc, const int32_t *rows, int nrows, int32_t *inv, int T,
                             int D, void *dh, hipStream_t st);
 
+// `bytes` from device to host memory (to_host) or back, in stream order: the
+// copy kernel of hostcopy.hip for pinned memory in whole aligned 16-byte
+// vectors, hipMemcpyAsync otherwise.
+hipError_t launch_host_copy(void *dst, const void *src, size_t bytes, bool to_host, hipStream_t st);
+
 // GEMM launch; `side` (may be NULL) adds the token-reduction workgroups.
 hipError_t launch_gemm(const GemmArgs &g, Dtype dt, bool b_kmajor, const SideArgs *side,
                        hipStream_t st);

@@ -106,3 +106,29 @@ def test_ckpt_stash_holds_the_inputs(orc):
     n0 = T * dims[0] * 2
     assert torch.equal(stash[:n0].view(torch.bfloat16).view(T, dims[0]), x0.cpu())
     assert torch.equal(stash[n0:n0 + T * dims[1] * 2].view(torch.bfloat16).view(T, dims[1]), x1.cpu())
+
+
+@pytest.mark.parametrize("T,offset", [(1, 0), (63, 0), (64, 8)])
+def test_ckpt_stash_copies(T, offset):
+    """The host copies at their edges: one token, whole and partial blocks of
+    vectors, and a stash at an address that only the byte copy takes.  Every
+    node's input must arrive whole, out and back."""
+    dims, ranks = [512, 256, 520], [8, 8]
+    _announce(f"ckpt stash T={T} offset={offset}")
+    nodes, x0, g = _chain_inputs(T, dims, ranks, seed=T)
+    ws_b, host_b = lm.lora_ckpt_sizes(nodes, T)
+    ws = torch.empty(ws_b, dtype=torch.uint8, device="cuda")
+    stash = torch.zeros(host_b + offset + 64, dtype=torch.uint8).pin_memory()
+    part = stash[offset:offset + host_b]
+    out = torch.empty(T, dims[-1], dtype=torch.bfloat16, device="cuda")
+    dx0 = torch.empty(T, dims[0], dtype=torch.bfloat16, device="cuda")
+    lm.lora_ckpt_forward(nodes, x0, out, part, ws)
+    torch.cuda.synchronize()
+    n0 = T * dims[0] * 2
+    assert torch.equal(part[:n0].view(torch.uint8), x0.cpu().view(torch.uint8).reshape(-1))
+    assert int(stash[:offset].sum()) == 0 and int(stash[offset + host_b:].sum()) == 0
+    lm.lora_ckpt_backward(nodes, g, dx0, part, ws)
+    torch.cuda.synchronize()
+    y, grads, dx = _plain(nodes, x0, g)
+    assert torch.equal(out, y) and torch.equal(dx0, dx)
+    assert all(torch.equal(nd["dA"], a) and torch.equal(nd["dB"], b) for nd, (a, b) in zip(nodes, grads))
