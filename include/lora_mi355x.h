@@ -244,6 +244,12 @@ lora_status_t lm_head_reduced_ce(const void *h, const void *W, int64_t T, int64_
  * ((size_t)-1 for rejected sizes).  Errors: LORA_EINVAL, LORA_EUNSUPPORTED
  * (D, sizes), LORA_EWORKSPACE, LORA_EHIP. */
 size_t topk_table_workspace_bytes(int64_t V, int64_t D, int64_t k);
+/* Workspace with which topk_table_build keeps the candidate lists of all V
+ * rows at once and so computes each similarity once instead of twice (about
+ * 57 KB a row; 7.4 GB at V = 128256, k = 1000); topk_table_workspace_bytes
+ * where that build does not pay.  Any smaller workspace of at least
+ * topk_table_workspace_bytes runs the build over batches of rows. */
+size_t topk_table_workspace_bytes_paired(int64_t V, int64_t D, int64_t k);
 lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, int32_t *table,
                                float *values, void *ws, size_t ws_bytes, void *hip_stream);
 

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -287,18 +288,19 @@ CeLayout ce_layout(int64_t T, int64_t D, int64_t nrows, int64_t nJ, bool want_dh
   return L;
 }
 
-// Top-k table workspace: row norms, and per batch of rows a threshold, a
-// count and a candidate list per row (TOPK_SLOTS minus the sort slots of the
-// final pass: room for k plus at least one column chunk, so that most chunks
-// need no selection).
-constexpr int64_t kTopkChunk = 4096, kTopkBatch = 16384;
+// Top-k table workspace: row norms, and per row a threshold, a count and a
+// candidate list (TOPK_SLOTS minus the sort slots of the final pass: room for
+// k plus at least one column chunk or block, so that most chunks need no
+// selection).  `paired` keeps the lists of all V rows at once, which lets each
+// product serve both of its rows; otherwise they are those of a batch of rows.
+constexpr int64_t kTopkChunk = TOPK_BLOCK, kTopkBatch = 16384;
 struct TopkLayout {
-  size_t rn, thr, cnt, val, idx, total;
+  size_t rn, thr, cnt, key, total;
   int64_t R, cap, lazy;
 };
-TopkLayout topk_layout(int64_t V, int64_t k) {
+TopkLayout topk_layout(int64_t V, int64_t k, bool paired) {
   TopkLayout L{};
-  L.R = std::min(V, kTopkBatch);
+  L.R = paired ? V : std::min(V, kTopkBatch);
   int64_t p2 = 1;
   while (p2 < k) p2 <<= 1;
   L.cap = (TOPK_SLOTS - p2) & ~3;  // >= k + kTopkChunk for every k <= 2048; whole vectors of 4
@@ -310,12 +312,19 @@ TopkLayout topk_layout(int64_t V, int64_t k) {
   off += round256((size_t)L.R * 4);
   L.cnt = off;
   off += round256((size_t)L.R * 4);
-  L.val = off;
-  off += round256((size_t)L.R * L.cap * 4);
-  L.idx = off;
-  off += round256((size_t)L.R * L.cap * 4);
+  L.key = off;
+  off += round256((size_t)L.R * L.cap * 8);
   L.total = off;
   return L;
+}
+// The paired build does half the products of the batched one on 256 x 256
+// tiles (155 against 70 ms at V = 128256, D = 3072, k = 1000).  Below one
+// block its single round is V / 256 tiles squared, halved, on 256 CUs, and
+// the 128 x 128 tiles of the batched build fill the chip as well or better.
+// Its lists take 57 KB a row; above 32 GiB the batched build's fixed amount is
+// taken instead.
+bool topk_paired(int64_t V, int64_t k) {
+  return V >= TOPK_BLOCK && topk_layout(V, k, true).total <= (size_t(32) << 30);
 }
 
 lora_status_t check_ws(void *ws, size_t ws_bytes, size_t need) {
@@ -873,7 +882,12 @@ size_t topk_table_workspace_bytes(int64_t V, int64_t D, int64_t k) {
   if (V < 1 || D < 8 || D % 8 || k < 1 || k > std::min<int64_t>(V, 2048) || D > kMaxDim ||
       V > kMaxElems / D || V > kMaxElems / k)
     return (size_t)-1;
-  return topk_layout(V, k).total;
+  return topk_layout(V, k, false).total;
+}
+
+size_t topk_table_workspace_bytes_paired(int64_t V, int64_t D, int64_t k) {
+  const size_t least = topk_table_workspace_bytes(V, D, k);
+  return least != (size_t)-1 && topk_paired(V, k) ? topk_layout(V, k, true).total : least;
 }
 
 lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, int32_t *table,
@@ -886,7 +900,8 @@ lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, i
     return fail(LORA_EUNSUPPORTED, "D at most 2^20 and W, table below 2^31 elements");
   if (!aligned16(W) || !aligned16(table) || (values && !aligned16(values)))
     return fail(LORA_EINVAL, "pointers must be 16-byte aligned");
-  const TopkLayout L = topk_layout(V, k);
+  const bool paired = topk_paired(V, k) && ws_bytes >= topk_layout(V, k, true).total;
+  const TopkLayout L = topk_layout(V, k, paired);
   lora_status_t s;
   if ((s = check_ws(ws, ws_bytes, L.total)) != LORA_OK) return s;
   std::vector<Range> ins = {rng(W, V * D * 2)};
@@ -897,7 +912,7 @@ lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, i
   char *wsb = (char *)ws;
   float *rn = (float *)(wsb + L.rn);
   TopkArgs ta{};
-  ta.val = (float *)(wsb + L.val); ta.idx = (int32_t *)(wsb + L.idx);
+  ta.key = (uint64_t *)(wsb + L.key);
   ta.cnt = (int *)(wsb + L.cnt); ta.thr = (float *)(wsb + L.thr);
   ta.cap = (int)L.cap; ta.k = (int)k; ta.lazy = (int)L.lazy; ta.table = table; ta.tvals = values;
   hipError_t e;
@@ -907,9 +922,32 @@ lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, i
     t.done();
     if (e != hipSuccess) return hip_fail(e, "topk_sim launch");
   }
+  if (paired) {
+    if ((e = launch_topk_reset(ta.thr, ta.cnt, (int)V, -FLT_MAX, st)) != hipSuccess) return hip_fail(e, "topk reset");
+    GemmArgs g{};
+    g.A = W; g.lda = D;
+    g.B = W; g.ldb = D;
+    g.M = (int)V; g.N = (int)V; g.K = (int)D;
+    g.rn_a = rn; g.rn_b = rn;
+    g.tk_thr = ta.thr; g.tk_cnt = ta.cnt; g.tk_key = ta.key; g.tk_cap = (int)L.cap;
+    const int rounds = topk_rounds(V);
+    for (int round = 0; round < rounds; ++round) {
+      {
+        Timed t(K_TOPK_SIM, st);
+        e = launch_topk_round(g, round, st);
+        t.done();
+        if (e != hipSuccess) return hip_fail(e, "topk_sim launch");
+      }
+      Timed t(K_TOPK_SELECT, st);
+      e = launch_topk_select(ta, (int)V, round == rounds - 1, st);
+      t.done();
+      if (e != hipSuccess) return hip_fail(e, "topk_select launch");
+    }
+    return LORA_OK;
+  }
   for (int64_t r0 = 0; r0 < V; r0 += L.R) {
     const int rb = (int)std::min<int64_t>(L.R, V - r0);
-    if ((e = launch_topk_reset(ta.thr, ta.cnt, rb, st)) != hipSuccess) return hip_fail(e, "topk reset");
+    if ((e = launch_topk_reset(ta.thr, ta.cnt, rb, -INFINITY, st)) != hipSuccess) return hip_fail(e, "topk reset");
     ta.row0 = r0;
     for (int64_t c0 = 0; c0 < V; c0 += kTopkChunk) {
       GemmArgs g{};
@@ -917,7 +955,7 @@ lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, i
       g.B = (const char *)W + c0 * D * 2; g.ldb = D;
       g.M = rb; g.N = (int)std::min<int64_t>(kTopkChunk, V - c0); g.K = (int)D;
       g.col0 = (int)c0; g.rn_a = rn + r0; g.rn_b = rn + c0;
-      g.tk_thr = ta.thr; g.tk_cnt = ta.cnt; g.tk_val = ta.val; g.tk_idx = ta.idx;
+      g.tk_thr = ta.thr; g.tk_cnt = ta.cnt; g.tk_key = ta.key;
       g.tk_cap = (int)L.cap;
       {
         Timed t(K_TOPK_SIM, st);

@@ -153,6 +153,22 @@ __device__ __forceinline__ void fz_done(unsigned long long *sync) {
   __hip_atomic_fetch_add(sync + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Pair `p` of round `round` of the similarity table's blocks (nb of them):
+// round 0 pairs every block with itself; rounds 1 .. n - 1 (n = nb rounded up
+// to even) are a round-robin tournament (the circle method), in which every
+// two blocks meet once and no block plays twice in a round, so a round adds
+// at most one block of candidates to any row.  False: a bye.
+__device__ __forceinline__ bool topk_pair(int round, int nb, int p, int &bi, int &bj) {
+  if (round == 0) {
+    bi = bj = p;
+    return p < nb;
+  }
+  const int n = nb + (nb & 1), k = round - 1;
+  bi = p == 0 ? n - 1 : (k + p) % (n - 1);
+  bj = p == 0 ? k : (k - p + n - 1) % (n - 1);
+  return bi < nb && bj < nb;
+}
+
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 template <int V>
@@ -300,7 +316,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   // ---- tile of this workgroup: XCD-contiguous, grouped by GM tile rows ----
   const int tiles_m = (g.M + BM - 1) / BM;
   const int tiles_n = (g.N + BN - 1) / BN;
-  const int ntiles = tiles_m * tiles_n;
+  const int ntiles = EPI == EPI_TOPK_PAIRS ? (int)gridDim.x : tiles_m * tiles_n;
   // The first `nside` workgroups (a multiple of 8, so the XCD of a tile
   // workgroup is unchanged) run the token-reduction side items; they start
   // first and overlap with the tiles.
@@ -366,9 +382,34 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   const int gsize = group_m * tiles_n;
   const int first_m = (t / gsize) * group_m;
   const int gm = min(tiles_m - first_m, group_m);
-  const int mt = first_m + (t % gsize) % gm;
-  const int nt = (t % gsize) / gm;
+  int mt = first_m + (t % gsize) % gm;
+  int nt = (t % gsize) / gm;
+  if constexpr (EPI == EPI_TOPK_PAIRS) {
+    // Tile t of a round of block pairs: pair t / (TM * TN), then groups of
+    // four tile rows (32 consecutive tiles, one XCD's round, share 16 panels).
+    constexpr int TM = TOPK_BLOCK / BM, TN = TOPK_BLOCK / BN, RN = BM / BN;
+    static_assert(TOPK_BLOCK % BM == 0 && BM % BN == 0 && TM % 4 == 0, "whole groups of tiles");
+    int bi, bj;
+    if (!topk_pair(g.tk_round, g.tk_blocks, t / (TM * TN), bi, bj)) return;
+    const int l = t % (TM * TN);
+    const int lm = l / (4 * TN) * 4 + l % 4, ln = l % (4 * TN) / 4;
+    // (uniform; readfirstlane keeps the divisions' results, and the buffer
+    // resources built from them, in SGPRs)
+    mt = __builtin_amdgcn_readfirstlane(bi * TM + lm);
+    nt = __builtin_amdgcn_readfirstlane(bj * TN + ln);
+    // past V, or below the diagonal of a block's square with itself
+    if (mt >= tiles_m || nt >= tiles_n || (bi == bj && lm > ln / RN)) return;
+  }
   const int m0 = mt * BM, n0 = nt * BN;
+
+  // Thread t's (1 / norm, threshold) of row t of the tile, then of its
+  // columns, loaded ahead of the main loop, which hides their latency.
+  float2 tk_rt;
+  if constexpr (EPI == EPI_TOPK_PAIRS) {
+    const int v = tid < BM ? m0 + tid : n0 + tid - BM;
+    tk_rt = make_float2(__builtin_nanf(""), __builtin_nanf(""));
+    if (tid < BM + BN && v < g.M) tk_rt = make_float2(g.rn_a[v], g.tk_thr[v]);
+  }
 
   // Optional sum of partial rank-r products for the rows of this tile row:
   // its BM x r elements are shared out over the tile row's workgroups, one
@@ -591,9 +632,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   // Stages kt < nk_main stream x/dy and W; the following ones stream the LoRA
   // operands (j = (kt - nk_main) * BKE ...).  The choice is a uniform select
   // of resources and offsets, so the step stays branch-free.
-  auto is_lora = [&](int kt) { return QB ? kt < nk_lora : kt >= nk_main; };
+  // (Only the tiles that store C have a LoRA step.)
+  auto is_lora = [&](int kt) { return EPI == EPI_STORE && (QB ? kt < nk_lora : kt >= nk_main); };
   auto stage_k0 = [&](int kt) {
-    return (QB ? (kt < nk_lora ? kt : kt - nk_lora) : (kt >= nk_main ? kt - nk_main : kt)) * BKE;
+    return (QB ? (kt < nk_lora ? kt : kt - nk_lora) : (is_lora(kt) ? kt - nk_main : kt)) * BKE;
   };
   auto load_A = [&](auto SET, int kt) {
     constexpr int S = decltype(SET)::value;
@@ -812,6 +854,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
+  // DUAL: even and odd k-slices are summed apart and added at the end, the
+  // precision of a k-split between two waves.
+  constexpr bool DUAL = EPI == EPI_TOPK_PAIRS;
+  f32x16 acc2[DUAL ? FM : 1][DUAL ? FN : 1];
+  if constexpr (DUAL) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc2[i][j][q] = 0.0f;
+  }
 
   // ---- MFMA fragments of one k-slice ------------------------------------------
   struct Frag {
@@ -1132,6 +1186,15 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
       for (int s2 = 0; s2 < SPW; ++s2) read_frags_d(BUF, s2, f[s2]);
     };
     auto mma_stage = [&](const Frag(&f)[SPW]) {
+      if constexpr (DUAL) {
+#pragma unroll
+        for (int s2 = 0; s2 < SPW; ++s2)
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) mma32(E(), (s2 % 2 ? acc2 : acc)[i][j], f[s2].b[j], f[s2].a[i]);
+        return;
+      }
 #pragma unroll
       for (int s2 = 0; s2 < SPW; ++s2) mma_frags(f[s2]);
     };
@@ -1588,19 +1651,132 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
     base = __shfl(base, l0);
     if (mine == 0) return;
     int slot = base + before;
-    float *vr = g.tk_val + (int64_t)m * g.tk_cap;
-    int32_t *ir = g.tk_idx + (int64_t)m * g.tk_cap;
+    uint64_t *kr = g.tk_key + (int64_t)m * g.tk_cap;
     for (int c = 0; c < CPT; ++c) {
       const int cc = c_lo + c;
       const float v = zr[cc] * ra * rbs[cc];
       if (cc < ncol && v > th) {
-        if (slot < g.tk_cap) {  // never past the list (the sizes rule it out)
-          vr[slot] = v;
-          ir[slot] = g.col0 + n0 + cc;
-        }
+        if (slot < g.tk_cap) kr[slot] = topk_key(v, g.col0 + n0 + cc);  // never past the list (the sizes rule it out)
         ++slot;
       }
     }
+    return;
+  }
+  if constexpr (EPI == EPI_TOPK_PAIRS) {
+    // Cosines c = z * rn[m] * rn[n] of this tile, each offered to row m's list
+    // and, the similarity being symmetric, to row n's (not in the tiles on
+    // the diagonal, which hold both orders of a pair).  Each wave works on its
+    // 64 x 64 block in registers.  Row role: a lane holds 32 columns of its
+    // row per block row i and lane ^ 32 the other 32; one atomic add per row
+    // of the wave reserves the slots.  Column role: the 32 lanes of a half
+    // hold one column; ballots count it over the wave's rows, the counts are
+    // gathered one column per lane, and one atomic instruction reserves the
+    // slots of all 64 columns.  Blocks arrive in no order of their indices, so
+    // a candidate that equals the threshold is kept too (its index may be the
+    // smaller one).  Rows and columns past the end, and the column role where
+    // it is off, compare with NaN.
+    static_assert(WK == 1 && WTN == 64 && BM + BN <= NT, "one column of the wave's block per lane");
+    const bool both = m0 / BM != n0 / BM;
+    float2 *rt = (float2 *)smem;  // (1 / norm, threshold) of the tile's rows, then of its columns
+    if (tid < BM + BN) {
+      if (tid >= BM && !both) tk_rt.y = __builtin_nanf("");
+      rt[tid] = tk_rt;
+    }
+    __syncthreads();
+    const int half = lane >> 5;
+    const int wc = wn * WTN;  // the wave's first column of the tile
+    float th[FM], tn[FN][16];
+    {
+      float ra[FM];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const float2 v = rt[wm * WTM + i * 32 + lrow];
+        ra[i] = v.x;
+        th[i] = v.y;
+      }
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          const float2 v = rt[BM + wc + j * 32 + 8 * (x / 4) + 4 * half + x % 4];
+          tn[j][x] = v.y;
+#pragma unroll
+          for (int i = 0; i < FM; ++i) acc[i][j][x] = (acc[i][j][x] + acc2[i][j][x]) * ra[i] * v.x;
+        }
+    }
+    // counts of both roles, then all the atomics, then the stores
+    int rc[FM], base[FM], cc = 0, cbase = 0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      rc[i] = 0;
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) rc[i] += acc[i][j][x] >= th[i];
+    }
+    if (both) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          int lo = 0, hi = 0;
+#pragma unroll
+          for (int i = 0; i < FM; ++i) {
+            const uint64_t mk = __ballot(acc[i][j][x] >= tn[j][x]);
+            lo += __builtin_popcount((uint32_t)mk);
+            hi += __builtin_popcount((uint32_t)(mk >> 32));
+          }
+          const int c = j * 32 + 8 * (x / 4) + x % 4;  // the low half's column; the high half's is c + 4
+          cc = lane == c ? lo : lane == c + 4 ? hi : cc;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = m0 + wm * WTM + i * 32 + lrow;
+      const int other = __shfl_xor(rc[i], 32);
+      base[i] = 0;
+      if (half == 0 && rc[i] + other > 0) base[i] = atomicAdd(g.tk_cnt + m, rc[i] + other);
+      rc[i] = half ? other : 0;  // entries of the row ahead of this lane's
+    }
+    if (cc > 0) cbase = atomicAdd(g.tk_cnt + n0 + wc + lane, cc);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = m0 + wm * WTM + i * 32 + lrow;
+      int slot = __shfl(base[i], lrow) + rc[i];
+      uint64_t *kr = g.tk_key + (int64_t)m * g.tk_cap;
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          const float v = acc[i][j][x];
+          if (v >= th[i]) {
+            if (slot < g.tk_cap)  // never past the list (the sizes rule it out)
+              kr[slot] = topk_key(v, n0 + wc + j * 32 + 8 * (x >> 2) + 4 * half + (x & 3));
+            ++slot;
+          }
+        }
+    }
+    if (!both) return;
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const int c = j * 32 + 8 * (x / 4) + x % 4;
+        const int blo = __builtin_amdgcn_readlane(cbase, c), bhi = __builtin_amdgcn_readlane(cbase, c + 4);
+        int slot = half ? bhi : blo;
+        uint64_t *kr = g.tk_key + (int64_t)(n0 + wc + c + 4 * half) * g.tk_cap;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const float v = acc[i][j][x];
+          const bool in = v >= tn[j][x];
+          const uint64_t mk = __ballot(in);
+          if (mk == 0) continue;
+          const uint32_t mlo = (uint32_t)mk, mhi = (uint32_t)(mk >> 32);
+          const int before = half ? __builtin_amdgcn_mbcnt_hi(mhi, 0) : __builtin_amdgcn_mbcnt_lo(mlo, 0);
+          if (in && slot + before < g.tk_cap) kr[slot + before] = topk_key(v, m0 + wm * WTM + i * 32 + lrow);
+          slot += __builtin_popcount(half ? mhi : mlo);
+        }
+      }
     return;
   }
   if constexpr (EPI == EPI_CE_DZ) {

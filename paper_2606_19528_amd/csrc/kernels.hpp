@@ -146,6 +146,14 @@ __device__ __forceinline__ void dma4(__amdgpu_buffer_rsrc_t rs, char *lds, uint3
 }
 #pragma clang diagnostic pop
 
+// Order key of a similarity-table candidate: larger = higher similarity, then
+// smaller token index; never 0.
+__device__ __forceinline__ uint64_t topk_key(float v, int32_t j) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const uint32_t o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((uint64_t)o << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)j);
+}
+
 __device__ __forceinline__ u32x4 ld16(const void *p) { return *(const u32x4 *)p; }
 __device__ __forceinline__ void st16(void *p, u32x4 v) { *(u32x4 *)p = v; }
 __device__ __forceinline__ u32x4 zero16() { return u32x4{0u, 0u, 0u, 0u}; }

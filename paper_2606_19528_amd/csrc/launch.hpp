@@ -103,15 +103,15 @@ struct GemmArgs {
   const float *lse;                 // EPI_CE_DZ
   float dscale;
   int c_accumulate;                 // EPI_F32: C fp32 += product instead of =
-  // EPI_TOPK: cosine = z * rn_a[m] * rn_b[n]; appended (value, col0 + n) to
-  // row m's list (tk_val / tk_idx, tk_cap slots, count tk_cnt[m]) when above
-  // tk_thr[m].
+  // EPI_TOPK: cosine = z * rn_a[m] * rn_b[n]; the key of (cosine, col0 + n) is
+  // appended to row m's list (tk_key, tk_cap slots, count tk_cnt[m]) when the
+  // cosine is above tk_thr[m].  EPI_TOPK_PAIRS: A = B = W, M = N = V, round
+  // tk_round of the pairs of tk_blocks blocks; appended to both rows' lists.
   const float *rn_a, *rn_b;
   const float *tk_thr;
   int *tk_cnt;
-  float *tk_val;
-  int32_t *tk_idx;
-  int tk_cap;
+  uint64_t *tk_key;
+  int tk_cap, tk_round, tk_blocks;
 };
 
 // Epilogues of launch_gemm_epi (bf16 operands, 128 x 128 tiles):
@@ -122,7 +122,9 @@ struct GemmArgs {
 //                 target]) for n < N, 0 for N <= n < ldc (B row-major);
 //   EPI_F32       C fp32 [M][ldc] (+)= A B (B k-major);
 //   EPI_TOPK      no C; candidates of the similarity table (B row-major).
-enum { EPI_STORE = 0, EPI_CE_STATS = 1, EPI_CE_DZ = 2, EPI_F32 = 3, EPI_TOPK = 4 };
+//   EPI_TOPK_PAIRS  the same for one round of block pairs, each product
+//                 serving both of its rows (256 x 256 tiles; launch_topk_round).
+enum { EPI_STORE = 0, EPI_CE_STATS = 1, EPI_CE_DZ = 2, EPI_F32 = 3, EPI_TOPK = 4, EPI_TOPK_PAIRS = 5 };
 hipError_t launch_gemm_epi(const GemmArgs &g, int epi, hipStream_t st);
 
 // Reduced vocabulary: J = sorted union over i < nrows of
@@ -154,9 +156,9 @@ hipError_t launch_ce_combine(const float *tmax, const float *tsum, int ntiles, i
 // entries rounded down to a multiple of 4, p2(k) the power of two at or
 // above k (at least k + 4096 for every k <= 2048).
 constexpr int TOPK_SLOTS = 8192;
+constexpr int TOPK_BLOCK = 4096;  // rows of a block of the paired build
 struct TopkArgs {
-  float *val;
-  int32_t *idx;
+  uint64_t *key;
   int *cnt;
   float *thr;
   int cap, k;
@@ -167,7 +169,12 @@ struct TopkArgs {
   int64_t row0;
 };
 hipError_t launch_row_rnorm(const void *W, int V, int D, float *rn, hipStream_t st);
-hipError_t launch_topk_reset(float *thr, int *cnt, int R, hipStream_t st);
+// thr[i] = lowest, cnt[i] = 0 for R rows.
+hipError_t launch_topk_reset(float *thr, int *cnt, int R, float lowest, hipStream_t st);
+// One round (0 .. topk_rounds - 1) of the paired build over all of W.
+inline int topk_blocks(int64_t V) { return (int)((V + TOPK_BLOCK - 1) / TOPK_BLOCK); }
+inline int topk_rounds(int64_t V) { const int nb = topk_blocks(V); return nb == 1 ? 1 : nb + (nb & 1); }
+hipError_t launch_topk_round(GemmArgs g, int round, hipStream_t st);
 // keep each of the R rows' k best candidates (final = 0) or sort them into
 // the table (final = 1); cap <= 8192, k <= 2048.
 hipError_t launch_topk_select(const TopkArgs &a, int R, int final, hipStream_t st);

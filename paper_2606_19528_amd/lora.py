@@ -90,6 +90,8 @@ def lib() -> ctypes.CDLL:
     L.lora_ckpt_backward.restype = i32
     L.topk_table_workspace_bytes.argtypes = [i64, i64, i64]
     L.topk_table_workspace_bytes.restype = sz
+    L.topk_table_workspace_bytes_paired.argtypes = [i64, i64, i64]
+    L.topk_table_workspace_bytes_paired.restype = sz
     L.topk_table_build.argtypes = [vp, i64, i64, i64, vp, vp, vp, sz, vp]
     L.topk_table_build.restype = i32
     L.lora_status_str.argtypes = [i32]
@@ -333,6 +335,13 @@ def topk_table_build(W, k: int, table=None, values=None, ws=None, stream=None):
     n = lib().topk_table_workspace_bytes(V, D, k)
     if n == ctypes.c_size_t(-1).value:
         raise LoraError(LORA_EINVAL, "topk_table_workspace_bytes", "sizes rejected")
+    if ws is None:
+        # the paired build's larger workspace where the device has room for it
+        paired = int(lib().topk_table_workspace_bytes_paired(V, D, k))
+        try:
+            ws, ws_bytes = _ws(None, paired, W, stream)
+        except torch.cuda.OutOfMemoryError:
+            ws = None
     ws, ws_bytes = _ws(ws, int(n), W, stream)
     st = lib().topk_table_build(_ptr(W), V, D, k, _ptr(table), _ptr(values), _ptr(ws), ws_bytes,
                                 _stream(stream))

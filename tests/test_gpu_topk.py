@@ -87,3 +87,45 @@ def test_topk_table_deterministic():
     b = lm.topk_table_build(W, 100)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("V,D,k", [(4095, 64, 40), (4096, 64, 2048), (4097, 72, 40), (8500, 64, 100),
+                                   (12300, 64, 64), (16400, 32, 1000)])
+def test_topk_table_paired_equals_batched(orc, V, D, k):
+    """From one block of 4096 rows the build runs rounds of block pairs, each
+    similarity serving both rows (one whole block, a ragged second block, an
+    odd number of blocks with a bye); given only the smaller workspace it runs
+    row batches.  Both agree with the oracle and, up to near-ties, with each
+    other; rows repeated far apart tie exactly, the smaller index first."""
+    _announce(f"topk paired V={V} D={D} k={k}")
+    W = _embeddings(V, D, seed=V)
+    W[V - 1] = W[3]
+    W[V // 2] = W[3]
+    Wd = W.cuda()
+    out = {}
+    for name, n in (("paired", lm.lib().topk_table_workspace_bytes_paired(V, D, k)),
+                    ("batched", lm.lib().topk_table_workspace_bytes(V, D, k))):
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        table = torch.empty(V, k, dtype=torch.int32, device="cuda")
+        values = torch.empty(V, k, dtype=torch.float32, device="cuda")
+        lm.topk_table_build(Wd, k, table, values, ws=ws)
+        torch.cuda.synchronize()
+        out[name] = (table.cpu(), values.cpu())
+    # the tile shapes sum in different orders: at most a few roundings apart
+    assert (out["paired"][1] - out["batched"][1]).abs().max() <= EPS
+    for table, values in out.values():
+        for i in (3, V // 2, V - 1):
+            assert table[i, :3].tolist() == [3, V // 2, V - 1]
+        rows = [i for i in sorted({0, 1, 255, 256, 2047, 4094, *range(5, V, 613), V - 2}) if i not in (3, V // 2, V - 1)]
+        _check_rows(orc, W, table, values, k, rows)
+
+
+def test_topk_table_paired_all_equal():
+    """Every similarity ties: each list overflows its threshold in every round,
+    and the k smallest indices must come out."""
+    V, D, k = 8300, 64, 20
+    _announce("topk all rows equal")
+    W = _embeddings(1, D, seed=1).repeat(V, 1).cuda()
+    table = lm.topk_table_build(W, k)
+    torch.cuda.synchronize()
+    assert torch.equal(table.cpu(), torch.arange(k, dtype=torch.int32).repeat(V, 1))
