@@ -139,6 +139,11 @@ lora_status_t lora_linear_bwd_noalloc(const void *x, const void *W, const void *
 lora_status_t frozen_linear_bwd_dx(const void *dy, const void *W, void *dx, int64_t T,
                                    int64_t d_in, int64_t d_out, lora_dtype_t dt, void *ws,
                                    size_t ws_bytes, void *hip_stream);
+/* Workspace with which frozen_linear_bwd_dx (and its quantized form) splits a
+ * long reduction over CUs that the output's tiles would leave idle; 0 where
+ * that does not pay, (size_t)-1 for rejected sizes.  Optional: with less, or
+ * none, the call runs unsplit. */
+size_t frozen_linear_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt);
 
 /* ---- Quantized frozen base ------------------------------------------------
  * The same three operations with W stored quantized and dequantized on the

@@ -628,9 +628,15 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   return LORA_OK;
 }
 
+size_t frozen_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt) {
+  const int n = dt == LORA_BF16 ? gemm_splits(T, d_in, d_out) : 1;
+  return n > 1 ? (size_t)n * T * d_in * 4 : 0;
+}
+
 lora_status_t frozen_impl(const void *dy, const void *W, const void *qc, const float *qs,
                           const float *qo, int bits, int64_t group, void *dx, int64_t T,
-                          int64_t d_in, int64_t d_out, lora_dtype_t dt, void *hip_stream) {
+                          int64_t d_in, int64_t d_out, lora_dtype_t dt, void *ws, size_t ws_bytes,
+                          void *hip_stream) {
   lora_status_t s = check_shapes(T, d_in, d_out, 0, dt);
   if (s != LORA_OK) return s;
   QWeight qw{};
@@ -655,8 +661,15 @@ lora_status_t frozen_impl(const void *dy, const void *W, const void *qc, const f
   g.M = (int)T; g.N = (int)d_in; g.K = (int)d_out;
   g.C = dx; g.ldc = d_in;
   set_qweight(g, qc ? &qw : nullptr);
+  // The workspace is optional here: with room for the planes of a split
+  // reduction (and clear of the operands) the split one runs.
+  const size_t planes = frozen_split_bytes(T, d_in, d_out, dt);
+  const Range wr = rng(ws, (int64_t)planes);
+  const bool split = planes > 0 && ws && ws_bytes >= planes && aligned16(ws) && !any_overlap({wr, outs[0]}, ins) &&
+                     (!qc || (qw.log2g >= 6 && gemm_q_direct(g, bits, true, false)));
   Timed t(qc ? K_GEMM_FROZEN_DX_Q : K_GEMM_FROZEN_DX, st);
-  hipError_t e = run_gemm(g, dt == LORA_BF16 ? DT_BF16 : DT_F32, qc ? &qw : nullptr, true, nullptr, st);
+  hipError_t e = split ? launch_gemm_split(g, qc ? bits : 16, (float *)ws, st)
+                       : run_gemm(g, dt == LORA_BF16 ? DT_BF16 : DT_F32, qc ? &qw : nullptr, true, nullptr, st);
   t.done();
   return e == hipSuccess ? LORA_OK : hip_fail(e, "gemm_frozen_dx launch");
 }
@@ -721,20 +734,21 @@ lora_status_t lora_linear_bwd_q(const void *x, const void *W_codes, const float 
 lora_status_t frozen_linear_bwd_dx(const void *dy, const void *W, void *dx, int64_t T,
                                    int64_t d_in, int64_t d_out, lora_dtype_t dt, void *ws,
                                    size_t ws_bytes, void *hip_stream) {
-  (void)ws;
-  (void)ws_bytes;
-  return frozen_impl(dy, W, nullptr, nullptr, nullptr, 0, 0, dx, T, d_in, d_out, dt, hip_stream);
+  return frozen_impl(dy, W, nullptr, nullptr, nullptr, 0, 0, dx, T, d_in, d_out, dt, ws, ws_bytes, hip_stream);
+}
+
+size_t frozen_linear_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt) {
+  if (check_shapes(T, d_in, d_out, 0, dt) != LORA_OK) return (size_t)-1;
+  return frozen_split_bytes(T, d_in, d_out, dt);
 }
 
 lora_status_t frozen_linear_bwd_dx_q(const void *dy, const void *W_codes, const float *W_scale,
                                      const float *W_offset, int bits, int64_t group, void *dx,
                                      int64_t T, int64_t d_in, int64_t d_out, void *ws,
                                      size_t ws_bytes, void *hip_stream) {
-  (void)ws;
-  (void)ws_bytes;
   if (!W_codes) return fail(LORA_EINVAL, "codes, scale and offset are required");
   return frozen_impl(dy, nullptr, W_codes, W_scale, W_offset, bits, group, dx, T, d_in, d_out,
-                     LORA_BF16, hip_stream);
+                     LORA_BF16, ws, ws_bytes, hip_stream);
 }
 
 size_t lm_head_workspace_bytes(int op, int64_t T, int64_t V, int64_t D, int64_t nrows,

@@ -40,6 +40,7 @@
 //    share of tiles is a compact block of GM tile rows.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "colred.hpp"
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   static_assert(BMODE != B_KMAJ_TR || ES == 2, "transposed LDS reads are bf16");
   static_assert(DMA ? (NBUF == 3 || NBUF == 4) : (NBUF == 2 || NBUF == 3), "LDS ring depth");
   static_assert(!QD || (NBUF == 3 && BN <= 256 && (BN / 64 + 1) * BKE <= 256 && QCW * QC_PW * 64 * NWV >= BKE * BN &&
-                        QRUNS * 2 * QB <= QSLOT && QRPT * NT * 2 * QB <= QSLOT && EPI == EPI_STORE &&
+                        QRUNS * 2 * QB <= QSLOT && QRPT * NT * 2 * QB <= QSLOT && (EPI == EPI_STORE || EPI == EPI_F32) &&
                         BKE % 16 == 0 && BN % 16 == 0 && QIPS < 64),
                 "quantized direct-to-LDS stages: a ring of three, whole runs of 16 weights");
   static_assert(!DMA || ((QB == 0 || DMA == 1) && ES == 2 && FS == 2 && (BKB == 128 || BKB == 64) && BMODE != B_KMAJ_REG &&
@@ -312,6 +313,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   const int wk = wave % WK;
   const int wn = (wave / WK) % WN;
   const int wm = wave / (WK * WN);
+
+  // Split reduction (launch_gemm_split): workgroups of grid row y sum the y-th
+  // range of k_chunk k-rows into the y-th fp32 plane of C.
+  const int k_rows = g.K;  // k-rows of the whole B
+  int k_first = 0;
+  if constexpr (EPI == EPI_F32 && BMODE == B_KMAJ_TR) {
+    if (g.k_chunk > 0) {
+      k_first = (int)blockIdx.y * g.k_chunk;
+      g.A = (const char *)g.A + (int64_t)k_first * ES;
+      g.B = (const char *)g.B + (int64_t)k_first * g.ldb * (QB ? QB : 8 * ES) / 8;
+      g.C = (float *)g.C + (int64_t)blockIdx.y * g.M * g.ldc;
+      g.K = min(g.k_chunk, g.K - k_first);
+    }
+  }
 
   // ---- tile of this workgroup: XCD-contiguous, grouped by GM tile rows ----
   const int tiles_m = (g.M + BM - 1) / BM;
@@ -568,7 +583,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
   const int qcol = BMODE == B_ROW ? (tid % (BKE / 16)) * 16 : (tid % (BN / 16)) * 16;
   const int64_t q_rowbytes = (int64_t)g.ldb * (QB ? QB : 8) / 8;
   const int64_t q_ldg = g.ldb >> g.qlog2g;  // groups per W row
-  const int q_wrows = BMODE == B_ROW ? g.N : g.K;
+  const int q_wrows = BMODE == B_ROW ? g.N : k_rows;
   __amdgpu_buffer_rsrc_t rsQ, rsQs, rsQo;
   if constexpr (QB) {
     if constexpr (BMODE == B_ROW) {
@@ -576,8 +591,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
       rsQ = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)g.B + n0 * q_rowbytes), (short)0,
                                               (int)(nrows * q_rowbytes), 0x00020000);
     }
-    rsQs = __builtin_amdgcn_make_buffer_rsrc((void *)g.qscale, (short)0, (int)(q_ldg * q_wrows * 4), 0x00020000);
-    rsQo = __builtin_amdgcn_make_buffer_rsrc((void *)g.qoffset, (short)0, (int)(q_ldg * q_wrows * 4), 0x00020000);
+    const int qbytes = (int)((q_ldg * q_wrows - k_first) * 4);
+    rsQs = __builtin_amdgcn_make_buffer_rsrc((void *)(g.qscale + k_first), (short)0, qbytes, 0x00020000);
+    rsQo = __builtin_amdgcn_make_buffer_rsrc((void *)(g.qoffset + k_first), (short)0, qbytes, 0x00020000);
   }
   // Quantized direct-to-LDS loads (QD): per lane, the offset of its code
   // chunk relative to the stage's first weight and the k position (row-major
@@ -1945,7 +1961,8 @@ static inline int pick_group_m(int tiles_m, int tiles_n, int BM, int BN) {
 
 template <class E, int BM, int BN, int WM, int WN, int WK, int BMODE, int BKB, int NBUF, int RD, int FS,
           int QB = 0, int EPI = EPI_STORE, int DMA = 0>
-static hipError_t launch_cfg(const GemmArgs &g, const SideArgs *side, hipStream_t st, FuseArgs *fz = nullptr) {
+static hipError_t launch_cfg(const GemmArgs &g, const SideArgs *side, hipStream_t st, FuseArgs *fz = nullptr,
+                             int splits = 1) {
   const int tm = g.M > 0 ? (g.M + BM - 1) / BM : 0, tn = (g.N + BN - 1) / BN;
   // Direct-to-LDS tiles address a k-major B2 with B's per-lane offsets.
   if (DMA && BMODE == B_KMAJ_TR && g.r > 0 && g.ldb2 != g.ldb) return hipErrorInvalidValue;
@@ -1974,7 +1991,7 @@ static hipError_t launch_cfg(const GemmArgs &g, const SideArgs *side, hipStream_
   if (BMODE == B_ROW && nside > 0) return hipErrorInvalidValue;  // side items run in k-major launches only
   const int grid = tm * tn + nside + fa.nwg;
   if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL((gemm_kernel<E, BM, BN, WM, WN, WK, BMODE, BKB, NBUF, RD, FS, QB, EPI, DMA>), dim3(grid),
+  hipLaunchKernelGGL((gemm_kernel<E, BM, BN, WM, WN, WK, BMODE, BKB, NBUF, RD, FS, QB, EPI, DMA>), dim3(grid, splits),
                      dim3(64 * WM * WN * WK), 0, st, g, tm > 0 ? pick_group_m(tm, tn, BM, BN) : 1,
                      sa, nside, fa);
   return hipGetLastError();
@@ -1994,18 +2011,45 @@ static hipError_t launch_cfg(const GemmArgs &g, const SideArgs *side, hipStream_
 // launches with token-reduction side items: with every CU holding a tile,
 // those run after the tiles instead of beside them (+7 % on such launches).
 // Returns 0: 128x128, 1: 256x128, 2: 256x256, 3: 128x64, 4: 256x192.
+constexpr double kEffKmaj[5] = {0.76, 1.04, 1.11, 0.47, 0.91}, kEffRow[5] = {0.84, 0.99, 1.02, 0.56, 0.88};
+static inline double tile_cost(int64_t M, int64_t N, int bm, int bn, double eff) {
+  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  return (double)((tiles + 255) / 256) * bm * bn / eff;
+}
 static inline int pick_shape(int M, int N, bool b_kmajor, bool with_side) {
-  auto cost = [&](int bm, int bn, double eff) {
-    const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    return (double)((tiles + 255) / 256) * bm * bn / eff;
-  };
-  const double c0 = cost(128, 128, b_kmajor ? 0.76 : 0.84), c1 = cost(256, 128, b_kmajor ? 1.04 : 0.99),
-               c2 = cost(256, 256, b_kmajor ? 1.11 : 1.02), c3 = cost(128, 64, b_kmajor ? 0.47 : 0.56),
-               c4 = cost(256, 192, b_kmajor ? 0.91 : 0.88);
+  const double *eff = b_kmajor ? kEffKmaj : kEffRow;
+  const double c0 = tile_cost(M, N, 128, 128, eff[0]), c1 = tile_cost(M, N, 256, 128, eff[1]),
+               c2 = tile_cost(M, N, 256, 256, eff[2]), c3 = tile_cost(M, N, 128, 64, eff[3]),
+               c4 = tile_cost(M, N, 256, 192, eff[4]);
   if (!with_side && c4 < c0 && c4 < c1 && c4 < c2 && c4 < c3) return 4;
   if (c3 < c0 && c3 < c1 && c3 < c2) return 3;
   if (c2 <= c1 && c2 <= c0) return 2;
   return c1 < c0 ? 1 : 0;
+}
+
+// Split reduction of a plain k-major product (the frozen dx) into fp32
+// planes, for outputs whose tiles would leave most CUs idle over a long
+// reduction: tiles of 128 x 128 up to 128 rows, else 256 x 256, and as many
+// ranges of k as fill the 256 CUs once, each of at least 1024 k-rows, at most
+// 32.  Costs as in pick_shape, times the k-rows, in units of a full-rate CU's
+// products; writing and reading the planes (8 bytes per element, about 4
+// TB/s) is 4.4 such units per element.  Measured at 1024 x 3072 over 128256:
+// 192 tiles of 128 x 128 unsplit 1124 us, 48 tiles of 256 x 256 x 5 ranges
+// 672 us.  Returns the number of ranges (1: no split) and the k-rows of each.
+static inline int split_plan(int64_t M, int64_t N, int64_t K, int *k_chunk) {
+  const int64_t b = M <= 128 ? 128 : 256;
+  const int64_t tiles = ((M + b - 1) / b) * ((N + b - 1) / b);
+  const int64_t n = std::min<int64_t>({tiles > 128 ? 1 : 256 / tiles, K / 1024, 32});
+  *k_chunk = (int)K;
+  if (n < 2) return 1;
+  const int64_t chunk = ((K + n - 1) / n + 63) / 64 * 64, np = (K + chunk - 1) / chunk;
+  static const int shp[5][2] = {{128, 128}, {256, 128}, {256, 256}, {128, 64}, {256, 192}};
+  const int c = pick_shape((int)M, (int)N, true, false);
+  const double whole = tile_cost(M, N, shp[c][0], shp[c][1], kEffKmaj[c]) * (double)K;
+  const double split = (double)b * b / kEffKmaj[b == 128 ? 0 : 2] * (double)chunk + 4.4 * (double)(M * N * np);
+  if (split > 0.9 * whole) return 1;
+  *k_chunk = (int)chunk;
+  return (int)np;
 }
 
 }  // namespace lora

@@ -30,6 +30,16 @@ static hipError_t launch_q_dma(const GemmArgs &g, int shape, bool kmaj, const Si
   }
 }
 
+hipError_t launch_gemm_split_q(const GemmArgs &g, int bits, int splits, hipStream_t st) {
+  if (g.M <= 128)
+    return bits == 4
+               ? launch_cfg<BF16, 128, 128, 2, 2, 2, B_KMAJ_TR, 128, 3, 3, 2, 4, EPI_F32, 1>(g, nullptr, st, nullptr, splits)
+               : launch_cfg<BF16, 128, 128, 2, 2, 2, B_KMAJ_TR, 128, 3, 3, 2, 8, EPI_F32, 1>(g, nullptr, st, nullptr, splits);
+  return bits == 4
+             ? launch_cfg<BF16, 256, 256, 2, 2, 1, B_KMAJ_TR, 64, 3, 3, 2, 4, EPI_F32, 1>(g, nullptr, st, nullptr, splits)
+             : launch_cfg<BF16, 256, 256, 2, 2, 1, B_KMAJ_TR, 64, 3, 3, 2, 8, EPI_F32, 1>(g, nullptr, st, nullptr, splits);
+}
+
 bool gemm_q_direct(const GemmArgs &g, int bits, bool b_kmajor, bool with_side) {
   // Groups of at least 64 weights (a row-major stage then holds one group per
   // row), the LoRA stages within the first three, and the scales (and, for

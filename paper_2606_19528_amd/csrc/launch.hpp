@@ -112,6 +112,7 @@ struct GemmArgs {
   int *tk_cnt;
   uint64_t *tk_key;
   int tk_cap, tk_round, tk_blocks;
+  int k_chunk;  // EPI_F32, k-major B: k-rows of one range of a split reduction, 0: not split
 };
 
 // Epilogues of launch_gemm_epi (bf16 operands, 128 x 128 tiles):
@@ -195,6 +196,14 @@ hipError_t launch_gemm(const GemmArgs &g, Dtype dt, bool b_kmajor, const SideArg
                        hipStream_t st);
 // bf16 GEMM whose B is the quantized frozen weight (bits = 4 or 8), dequantized
 // into LDS; the LoRA step (r <= 64) runs first.
+// Ranges of k that launch_gemm_split sums apart for a plain k-major product
+// (1: it does not pay), and the product itself (bits 16: bf16 B, else
+// quantized): C bf16 = sum over the ranges, in ascending order, of their fp32
+// planes [ranges][M][N] at `planes`.
+int gemm_splits(int64_t M, int64_t N, int64_t K);
+hipError_t launch_gemm_split(GemmArgs g, int bits, float *planes, hipStream_t st);
+hipError_t launch_gemm_split_q(const GemmArgs &g, int bits, int splits, hipStream_t st);
+
 // Whether launch_gemm_q runs the dequantizing direct-to-LDS tiles for g.
 bool gemm_q_direct(const GemmArgs &g, int bits, bool b_kmajor, bool with_side);
 hipError_t launch_gemm_q(const GemmArgs &g, int bits, bool b_kmajor, const SideArgs *side,

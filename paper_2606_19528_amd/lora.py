@@ -90,6 +90,8 @@ def lib() -> ctypes.CDLL:
     L.lora_ckpt_backward.restype = i32
     L.topk_table_workspace_bytes.argtypes = [i64, i64, i64]
     L.topk_table_workspace_bytes.restype = sz
+    L.frozen_linear_split_bytes.argtypes = [i64, i64, i64, ctypes.c_int]
+    L.frozen_linear_split_bytes.restype = sz
     L.topk_table_workspace_bytes_paired.argtypes = [i64, i64, i64]
     L.topk_table_workspace_bytes_paired.restype = sz
     L.topk_table_build.argtypes = [vp, i64, i64, i64, vp, vp, vp, sz, vp]
@@ -167,6 +169,17 @@ def _ws(ws, nbytes: int, like, stream=None):
     return ws, ws.numel() * ws.element_size()
 
 
+def _ws_optional(nbytes: int, like, stream=None):
+    """A temporary workspace that speeds a call up but is not needed by it:
+    None where the device has no room."""
+    import torch
+
+    try:
+        return _ws(None, nbytes, like, stream)[0]
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def lora_linear_workspace_bytes(op: int, T: int, d_in: int, d_out: int, r: int, dt: int) -> int:
     n = lib().lora_linear_workspace_bytes(op, T, d_in, d_out, r, dt)
     if n == ctypes.c_size_t(-1).value:
@@ -215,11 +228,18 @@ def lora_linear_bwd_noalloc(x, W, A, B, u_saved, dy, dx, dA, dB, scale: float = 
     return dx, dA, dB
 
 
+def _split_ws(T, d_in, d_out, dt, like, stream):
+    n = lib().frozen_linear_split_bytes(T, d_in, d_out, dt)
+    return None if n == 0 or n == ctypes.c_size_t(-1).value else _ws_optional(int(n), like, stream)
+
+
 def frozen_linear_bwd_dx(dy, W, dx, ws=None, stream=None):
     """Rank-0 frozen linear input gradient dx = dy W."""
     T, d_out = dy.shape
     d_in = W.shape[1]
     dt = _dtype_code(dy)
+    if ws is None:
+        ws = _split_ws(T, d_in, d_out, dt, dy, stream)
     st = lib().frozen_linear_bwd_dx(_ptr(dy), _ptr(W), _ptr(dx), T, d_in, d_out, dt, _ptr(ws),
                                     0 if ws is None else ws.numel() * ws.element_size(),
                                     _stream(stream))
@@ -270,6 +290,8 @@ def frozen_linear_bwd_dx_q(dy, Wq, dx, ws=None, stream=None):
     """frozen_linear_bwd_dx with W quantized (dict, see _qw)."""
     codes, sc, off, bits, group, d_out, d_in = _qw(Wq)
     T = dy.shape[0]
+    if ws is None:
+        ws = _split_ws(T, d_in, d_out, LORA_BF16, dy, stream)
     st = lib().frozen_linear_bwd_dx_q(_ptr(dy), _ptr(codes), _ptr(sc), _ptr(off), bits, group,
                                       _ptr(dx), T, d_in, d_out, _ptr(ws),
                                       0 if ws is None else ws.numel() * ws.element_size(),
@@ -336,12 +358,7 @@ def topk_table_build(W, k: int, table=None, values=None, ws=None, stream=None):
     if n == ctypes.c_size_t(-1).value:
         raise LoraError(LORA_EINVAL, "topk_table_workspace_bytes", "sizes rejected")
     if ws is None:
-        # the paired build's larger workspace where the device has room for it
-        paired = int(lib().topk_table_workspace_bytes_paired(V, D, k))
-        try:
-            ws, ws_bytes = _ws(None, paired, W, stream)
-        except torch.cuda.OutOfMemoryError:
-            ws = None
+        ws = _ws_optional(int(lib().topk_table_workspace_bytes_paired(V, D, k)), W, stream)
     ws, ws_bytes = _ws(ws, int(n), W, stream)
     st = lib().topk_table_build(_ptr(W), V, D, k, _ptr(table), _ptr(values), _ptr(ws), ws_bytes,
                                 _stream(stream))
