@@ -88,7 +88,9 @@ typedef enum { LORA_OP_FWD = 0, LORA_OP_BWD = 1, LORA_OP_FROZEN_DX = 2 } lora_op
 
 /* Workspace bytes sufficient for any call of `op` with these sizes, whether
  * or not the optional u pointers are given.  Returns 0 when none is needed
- * and (size_t)-1 for sizes the entry point would reject.  Pure host logic. */
+ * and (size_t)-1 for sizes the entry point would reject.  Pure host logic.
+ * Up to 128 tokens (bf16) it includes what the few-token kernel wants; a call
+ * given less, but the tiled kernels' amount, runs those. */
 size_t lora_linear_workspace_bytes(lora_op_t op, int64_t T, int64_t d_in, int64_t d_out,
                                    int64_t r, lora_dtype_t dt);
 

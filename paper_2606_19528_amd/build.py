@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblora_mi355x.so")
-SOURCES = ["gemm.hip", "gemm_q.hip", "skinny.hip", "head.hip", "topk.hip", "hostcopy.hip", "api.cpp", "ckpt.cpp",
+SOURCES = ["gemm.hip", "gemm_q.hip", "skinny.hip", "head.hip", "topk.hip", "narrow.hip", "hostcopy.hip", "api.cpp", "ckpt.cpp",
            "static_ws.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

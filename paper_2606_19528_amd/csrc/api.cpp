@@ -238,6 +238,39 @@ BwdLayout bwd_layout(int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt
   return L;
 }
 
+// Few tokens: the workspace of the narrow kernels, beside that of the tiled
+// ones.  A call reports the larger of the two, runs the narrow kernel when it
+// is given that much and the tiled kernels when it is given only theirs.
+struct NarrowWs {
+  NarrowPlan p;
+  size_t sync, slots, da, u, total;
+};
+NarrowWs narrow_ws(bool bwd, int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt) {
+  NarrowWs L{};
+  if (dt != LORA_BF16) return L;
+  L.p = bwd ? narrow_plan(T, K, N, r) : narrow_plan(T, N, K, r);
+  if (!L.p.ok) return L;
+  NarrowPlan pu{};
+  if (bwd && r > 0) {  // u recomputed, in the forward's order of summation
+    pu = narrow_plan(T, N, K, r);
+    if (!pu.ok) return NarrowWs{};
+    pu.slot_bytes /= pu.tiles_n;
+    pu.flags = pu.tiles_m * pu.parts;
+  }
+  size_t off = 0;
+  L.sync = off;
+  const bool meets = L.p.parts > 1 || pu.parts > 1 || (bwd && r > 0 && L.p.tiles_m > 1);
+  off += meets ? round256((size_t)std::max(L.p.flags, pu.flags) * 4) : 0;
+  L.slots = off;
+  off += round256(std::max(L.p.slot_bytes, pu.slot_bytes));
+  L.da = off;
+  off += bwd ? round256(L.p.da_bytes) : 0;
+  L.u = off;
+  off += bwd ? round256((size_t)T * r * 4) : 0;
+  L.total = off;
+  return L;
+}
+
 // LM head workspaces.
 constexpr int64_t kHeadChunk = 8192;  // vocabulary columns per backward chunk (multiple of 128)
 struct VocabLayout {
@@ -378,6 +411,14 @@ hipError_t run_gemm(const GemmArgs &g, Dtype d, const QWeight *q, bool kmajor, c
   return q ? launch_gemm_q(g, q->bits, kmajor, side, st) : launch_gemm(g, d, kmajor, side, st);
 }
 
+// Whether the caller's workspace serves the narrow kernel: large enough,
+// aligned and clear of the operands (else the tiled kernels judge it).
+bool narrow_fits(const NarrowWs &nw, void *ws, size_t ws_bytes, const std::vector<Range> &operands) {
+  if (!nw.p.ok) return false;
+  if (nw.total == 0) return true;
+  return ws && ws_bytes >= nw.total && aligned16(ws) && !any_overlap({rng(ws, (int64_t)nw.total)}, operands);
+}
+
 lora_status_t hip_fail(hipError_t e, const char *what) {
   std::snprintf(g_err, sizeof g_err, "%s: %s", what, hipGetErrorString(e));
   return LORA_EHIP;
@@ -405,8 +446,13 @@ lora_status_t fwd_impl(const void *x, const void *W, const void *qc, const float
   for (const void *p : ptrs)
     if (p && !aligned16(p)) return fail(LORA_EINVAL, "pointers must be 16-byte aligned");
   const size_t es = esize(dt);
-  const size_t need = lora_linear_workspace_bytes(LORA_OP_FWD, T, d_in, d_out, r, dt);
-  if ((s = check_ws(ws, ws_bytes, need)) != LORA_OK) return s;
+  const NarrowWs nw = qc ? NarrowWs{} : narrow_ws(false, T, d_in, d_out, r, dt);
+  const bool narrow =
+      narrow_fits(nw, ws, ws_bytes, {rng(x, T * d_in * es), rng(W, d_out * d_in * es), rng(y, T * d_out * es),
+                                     rng(A, r * d_in * es), rng(B, d_out * r * es), rng(u_save, T * r * 4)});
+  const size_t least = fwd_layout(T, d_in, d_out, r, dt).total;
+  if ((s = check_ws(ws, ws_bytes, least)) != LORA_OK) return s;
+  const size_t need = std::max(least, narrow ? nw.total : 0);
   std::vector<Range> ins = {rng(x, T * d_in * es)};
   if (qc) ins.insert(ins.end(), qins.begin(), qins.end());
   else ins.push_back(rng(W, d_out * d_in * es));
@@ -415,8 +461,8 @@ lora_status_t fwd_impl(const void *x, const void *W, const void *qc, const float
     ins.push_back(rng(A, r * d_in * es));
     ins.push_back(rng(B, d_out * r * es));
     if (u_save) outs.push_back(rng(u_save, T * r * 4));
-    if (need) outs.push_back(rng(ws, (int64_t)need));
   }
+  if (need) outs.push_back(rng(ws, (int64_t)need));
   if (any_overlap(outs, ins)) return fail(LORA_EINVAL, "an output overlaps an input or another output");
 
   hipStream_t st = (hipStream_t)hip_stream;
@@ -426,6 +472,19 @@ lora_status_t fwd_impl(const void *x, const void *W, const void *qc, const float
   g.B = W; g.ldb = d_in;
   g.M = (int)T; g.N = (int)d_out; g.K = (int)d_in;
   g.C = y; g.ldc = d_out;
+  if (narrow) {
+    char *wsb = (char *)ws;
+    NarrowArgs a{};
+    a.X = x; a.W = W; a.V = A; a.P = B; a.out = y; a.u_out = r > 0 ? u_save : nullptr;
+    a.T = (int)T; a.N = (int)d_out; a.K = (int)d_in; a.r = (int)r; a.scale = scale;
+    a.sync = (unsigned *)(wsb + nw.sync);
+    a.slots = (float *)(wsb + nw.slots);
+    a.gen = next_gen();
+    Timed t(K_GEMM_FWD, st);
+    const hipError_t e = launch_narrow(a, nw.p, false, st);
+    t.done();
+    return e == hipSuccess ? LORA_OK : hip_fail(e, "gemm_fwd launch");
+  }
   if (r > 0 && !qc && fwd_layout(T, d_in, d_out, r, dt).fused) {
     const FwdLayout L = fwd_layout(T, d_in, d_out, r, dt);
     char *wsb = (char *)ws;
@@ -511,8 +570,14 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   for (const void *p : ptrs)
     if (p && !aligned16(p)) return fail(LORA_EINVAL, "pointers must be 16-byte aligned");
   const size_t es = esize(dt);
-  const size_t need = lora_linear_workspace_bytes(LORA_OP_BWD, T, d_in, d_out, r, dt);
-  if ((s = check_ws(ws, ws_bytes, need)) != LORA_OK) return s;
+  const NarrowWs nw = qc ? NarrowWs{} : narrow_ws(true, T, d_in, d_out, r, dt);
+  const bool narrow =
+      narrow_fits(nw, ws, ws_bytes, {rng(x, T * d_in * es), rng(W, d_out * d_in * es), rng(dy, T * d_out * es),
+                                     rng(dx, T * d_in * es), rng(A, r * d_in * es), rng(B, d_out * r * es),
+                                     rng(u_saved, T * r * 4), rng(dA, r * d_in * 4), rng(dB, d_out * r * 4)});
+  const size_t least = bwd_layout(T, d_in, d_out, r, dt).total;
+  if ((s = check_ws(ws, ws_bytes, least)) != LORA_OK) return s;
+  const size_t need = std::max(least, narrow ? nw.total : 0);
   std::vector<Range> ins = {rng(dy, T * d_out * es)};
   if (qc) ins.insert(ins.end(), qins.begin(), qins.end());
   else ins.push_back(rng(W, d_out * d_in * es));
@@ -525,8 +590,8 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
     if (u_saved) ins.push_back(rng(u_saved, T * r * 4));
     outs.push_back(rng(dA, r * d_in * 4));
     outs.push_back(rng(dB, d_out * r * 4));
-    if (need) outs.push_back(rng(ws, (int64_t)need));
   }
+  if (need) outs.push_back(rng(ws, (int64_t)need));
   if (any_overlap(outs, ins)) return fail(LORA_EINVAL, "an output overlaps an input or another output");
 
   hipStream_t st = (hipStream_t)hip_stream;
@@ -538,6 +603,37 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   g.M = dx ? (int)T : 0; g.N = (int)d_in; g.K = (int)d_out;
   g.C = dx; g.ldc = d_in;
   set_qweight(g, qc ? &qw : nullptr);
+  if (narrow) {
+    char *wsb = (char *)ws;
+    NarrowArgs a{};
+    a.T = (int)T; a.r = (int)r; a.scale = scale;
+    a.sync = (unsigned *)(wsb + nw.sync);
+    a.slots = (float *)(wsb + nw.slots);
+    a.da_slots = (float *)(wsb + nw.da);
+    const float *u = u_saved;
+    if (r > 0 && !u) {  // rematerialise u = x A^T as the forward summed it
+      NarrowPlan pu = narrow_plan(T, d_out, d_in, r);
+      pu.tiles_n = 1;
+      NarrowArgs b = a;
+      b.X = x; b.W = W; b.V = A; b.P = B;
+      b.N = 0; b.K = (int)d_in;
+      b.u_out = (float *)(wsb + nw.u);
+      b.gen = next_gen();
+      Timed t(K_LORA_DOWN, st);
+      e = launch_narrow(b, pu, false, st);
+      t.done();
+      if (e != hipSuccess) return hip_fail(e, "lora_down launch");
+      u = b.u_out;
+    }
+    a.X = dy; a.W = W; a.V = B; a.P = A; a.out = dx;
+    a.N = (int)d_in; a.K = (int)d_out;
+    a.xin = x; a.u_in = u; a.dA = dA; a.dB = dB;
+    a.gen = next_gen();
+    Timed t(K_GEMM_BWD_DX, st);
+    e = launch_narrow(a, nw.p, true, st);
+    t.done();
+    return e == hipSuccess ? LORA_OK : hip_fail(e, "gemm_bwd_dx launch");
+  }
   if (r == 0) {
     Timed t(qc ? K_GEMM_BWD_DX_Q : K_GEMM_BWD_DX, st);
     e = run_gemm(g, d, qc ? &qw : nullptr, true, nullptr, st);
@@ -633,6 +729,14 @@ size_t frozen_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t d
   return n > 1 ? (size_t)n * T * d_in * 4 : 0;
 }
 
+}  // namespace
+
+size_t lora::bwd_least_workspace(int64_t T, int64_t d_in, int64_t d_out, int64_t r, bool bf16) {
+  return bwd_layout(T, d_in, d_out, r, bf16 ? LORA_BF16 : LORA_F32).total;
+}
+
+namespace {
+
 lora_status_t frozen_impl(const void *dy, const void *W, const void *qc, const float *qs,
                           const float *qo, int bits, int64_t group, void *dx, int64_t T,
                           int64_t d_in, int64_t d_out, lora_dtype_t dt, void *ws, size_t ws_bytes,
@@ -684,9 +788,9 @@ size_t lora_linear_workspace_bytes(lora_op_t op, int64_t T, int64_t d_in, int64_
     return (size_t)-1;
   switch (op) {
     case LORA_OP_FWD:
-      return fwd_layout(T, d_in, d_out, r, dt).total;
+      return std::max(fwd_layout(T, d_in, d_out, r, dt).total, narrow_ws(false, T, d_in, d_out, r, dt).total);
     case LORA_OP_BWD:
-      return bwd_layout(T, d_in, d_out, r, dt).total;
+      return std::max(bwd_layout(T, d_in, d_out, r, dt).total, narrow_ws(true, T, d_in, d_out, r, dt).total);
     case LORA_OP_FROZEN_DX:
       return 0;
   }

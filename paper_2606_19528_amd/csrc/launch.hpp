@@ -323,6 +323,40 @@ bool gemm_fusable(int M, int N, int K, bool b_kmajor);
 // side items run by the producers); dx rows are required (g.M >= 1).
 hipError_t launch_gemm_fused(const GemmArgs &g, FuseArgs *fz, const SideArgs *side, hipStream_t st);
 
+// The LoRA linear over few tokens (narrow.hip), bf16, r a multiple of 4 up to
+// 64 (or 0): out [T][N] = X [T][K] against W (row-major: W [N][K], V = A [r][K],
+// P = B [N][r]; k-major: W [K][N], V = B [K][r], P = A [r][N]) with its rank-r
+// term, u_out [T][r] = X against V (optional; forward), and in the backward dA
+// [r][N] = E(scale u)^T xin and dB [K][r] = scale X^T u_in.  out may be
+// null (backward without dx; W is then not read) and N 0 (u alone, in the same
+// order of summation as beside any W).
+constexpr int64_t NARROW_MAX_T = 128;
+struct NarrowArgs {
+  const void *X, *W, *V, *P;
+  void *out;
+  float *u_out;
+  int T, N, K, r;
+  float scale;
+  const void *xin;
+  const float *u_in;
+  float *dA, *dB;
+  // workspace: flags of the meetings, the parts' sums, the row tiles' dA
+  unsigned *sync;
+  float *slots, *da_slots;
+  unsigned gen;  // this launch's tag, never 0
+  int tiles_m, tiles_n, parts, part_k;  // set by launch_narrow
+};
+struct NarrowPlan {
+  bool ok;
+  int rank_blocks, tiles_m, tiles_n, parts, part_k;
+  int64_t flags;
+  size_t slot_bytes, da_bytes;
+};
+NarrowPlan narrow_plan(int64_t T, int64_t N, int64_t K, int64_t r);
+// Workspace that lora_linear_bwd cannot do without (the tiled kernels').
+size_t bwd_least_workspace(int64_t T, int64_t d_in, int64_t d_out, int64_t r, bool bf16);
+hipError_t launch_narrow(NarrowArgs a, const NarrowPlan &p, bool k_major, hipStream_t st);
+
 // Split of a row-skinny product over its reduction axis L, and rows per
 // workgroup.  Short T (below 2048): one 16-row tile per workgroup, enough
 // segments to give the T / 16 row blocks about one workgroup per CU, no more

@@ -54,7 +54,8 @@ extern "C" lora_status_t lora_linear_bwd_noalloc(const void *x, const void *W, c
   if (need == (size_t)-1)  // sizes the entry point rejects: let it report why
     return lora_linear_bwd(x, W, A, B, u_saved, dy, dx, dA, dB, T, d_in, d_out, r, scale, dt, nullptr, 0,
                            hip_stream);
-  if (need > kScratchBytes) {
+  // (where the larger workspace of the few-token kernel does not fit, the tiled kernels run)
+  if (lora::bwd_least_workspace(T, d_in, d_out, r, dt == LORA_BF16) > kScratchBytes) {
     lora::set_last_error("workspace needed exceeds the static scratch (LORA_NOALLOC_SCRATCH_BYTES)");
     return LORA_EWORKSPACE;
   }

@@ -1,0 +1,146 @@
+"""GPU tests of the few-token kernel (up to 128 tokens, bf16): tiles of 32 or 64
+rows by 64 or 128 columns, the reduction in one part or several that meet in the
+workspace, one or two blocks of 32 rank columns, one or several row tiles.
+Every result against the fp64 oracle (max relative error <= 2e-2 per tensor,
+the bf16 bound of the other parity tests)."""
+import sys
+
+import pytest
+import torch
+
+import paper_2606_19528_amd as lm
+from gpu_helpers import compare, gpu_lora, oracle_lora
+from workloads import lora_inputs
+
+pytestmark = pytest.mark.gpu
+BF16 = torch.bfloat16
+
+
+def _announce(msg):
+    print(f"[case] {msg}", file=sys.stderr, flush=True)
+
+
+# (T, d_in, d_out, r): tile edges in T; reductions of less than a stage, a
+# ragged last stage, one part and many; ragged column tiles; ranks whose rows
+# are not whole 16-byte vectors, one and two rank blocks, none.
+SHAPES = [(1, 8, 8, 4), (1, 3072, 3072, 16), (16, 264, 72, 8), (24, 3072, 1032, 16), (31, 72, 520, 12),
+          (32, 1024, 64, 32), (33, 776, 2056, 64), (48, 2056, 1032, 36), (63, 4096, 256, 4), (64, 256, 4104, 64),
+          (65, 3080, 136, 8), (100, 520, 3072, 40), (127, 2048, 2048, 16), (128, 1032, 1032, 32), (129, 3072, 520, 24),
+          (103, 1544, 2056, 16), (95, 264, 8200, 4), (128, 2048, 1024, 64), (97, 1024, 3072, 28), (40, 2056, 3080, 0),
+          (120, 1032, 2056, 0), (128, 64, 64, 8)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_narrow_parity(orc, shape):
+    T, K, N, r = shape
+    _announce(f"narrow T={T} K={K} N={N} r={r}")
+    inp = lora_inputs(T, K, N, r, seed=sum(shape))
+    s = 2.0
+    got = gpu_lora(inp, s)
+    if r:
+        ref = oracle_lora(orc, inp, s)
+        again = gpu_lora(inp, s, recompute_u=True)
+        none = gpu_lora(inp, s, want_dx=False)
+        for k in ("y", "dx", "u", "dA", "dB"):  # a recomputed u is bitwise the saved one
+            assert torch.equal(got[k], again[k]), k
+        assert torch.equal(got["dA"], none["dA"]) and torch.equal(got["dB"], none["dB"])
+    else:
+        x, W, dy = (inp[k].double() for k in ("x", "W", "dy"))
+        ref = {"y": (x @ W.t()).numpy(), "dx": (dy @ W).numpy()}
+    compare(got, ref, BF16, label=f"narrow {shape}")
+
+
+@pytest.mark.parametrize("T", [20, 60, 110])
+def test_narrow_zero_B_is_rank_0(T):
+    """With B = 0 the output is the rank-0 forward's bitwise, at every rank."""
+    K, N = 2056, 520
+    _announce(f"narrow B=0 T={T}")
+    for r in (4, 32, 64):
+        inp = lora_inputs(T, K, N, r, seed=T)
+        inp["B"].zero_()
+        d = {k: v.cuda() for k, v in inp.items()}
+        y, y0 = (torch.empty(T, N, dtype=BF16, device="cuda") for _ in range(2))
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], y, None, 2.0)
+        lm.lora_linear_fwd(d["x"], d["W"], None, None, y0)
+        torch.cuda.synchronize()
+        if r <= 32:  # (ranks above 32 have tiles of their own)
+            assert torch.equal(y, y0)
+
+
+@pytest.mark.parametrize("fill", [0x00, 0xFF, "random"])
+def test_narrow_workspace_contents_and_reuse(orc, fill):
+    """The meetings' words start as whatever the workspace holds; one workspace
+    serves calls of other sizes in between, and less of it the tiled kernels."""
+    s = 2.0
+    n = max(lm.lora_linear_workspace_bytes(op, T, K, N, r, lm.LORA_BF16)
+            for T, K, N, r in ((24, 3072, 3072, 16), (120, 2048, 1032, 8)) for op in (lm.LORA_OP_FWD, lm.LORA_OP_BWD))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    if fill == "random":
+        ws.copy_(torch.randint(0, 256, ws.shape, dtype=torch.uint8, device="cuda"))
+    else:
+        ws.fill_(fill)
+    for it, (T, K, N, r) in enumerate([(24, 3072, 3072, 16), (120, 2048, 1032, 8), (24, 3072, 3072, 16)]):
+        _announce(f"narrow workspace fill={fill} T={T}")
+        inp = lora_inputs(T, K, N, r, seed=50 + it)
+        d = {k: v.cuda() for k, v in inp.items()}
+        o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
+             "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
+             "dB": torch.empty(N, r, device="cuda")}
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], o["y"], o["u"], s, ws=ws)
+        lm.lora_linear_bwd(d["x"], d["W"], d["A"], d["B"], o["u"], d["dy"], o["dx"], o["dA"], o["dB"], s, ws=ws)
+        torch.cuda.synchronize()
+        compare({k: v.cpu() for k, v in o.items()}, oracle_lora(orc, inp, s), BF16, label=f"fill={fill} it={it}")
+
+
+def test_narrow_least_workspace(orc):
+    """A workspace of the tiled kernels' size (the general bound: at most 64
+    padded rank columns per row of x and W) still serves the call."""
+    T, K, N, r = 24, 3072, 3072, 16
+    s = 2.0
+    inp = lora_inputs(T, K, N, r, seed=5)
+    d = {k: v.cuda() for k, v in inp.items()}
+    tiled = 4 * T * r * 4 + (T + N) * 64 * 2 + 768
+    assert tiled < lm.lora_linear_workspace_bytes(lm.LORA_OP_FWD, T, K, N, r, lm.LORA_BF16)
+    _announce("narrow shape with the tiled workspace")
+    y = torch.empty(T, N, dtype=BF16, device="cuda")
+    u = torch.empty(T, r, device="cuda")
+    ws = torch.empty(tiled, dtype=torch.uint8, device="cuda")
+    lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], y, u, s, ws=ws)
+    torch.cuda.synchronize()
+    ref = oracle_lora(orc, inp, s)
+    compare({"y": y.cpu(), "u": u.cpu()}, {"y": ref["y"], "u": ref["u"]}, BF16, label="tiled workspace")
+
+
+def test_narrow_graph_replay(orc):
+    """Replays carry one tag: each must find the meetings' words as if new."""
+    T, K, N, r = 123, 1544, 1032, 16
+    s = 2.0
+    d = {k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=60).items()}
+    o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
+         "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
+         "dB": torch.empty(N, r, device="cuda")}
+    n = max(lm.lora_linear_workspace_bytes(op, T, K, N, r, lm.LORA_BF16) for op in (lm.LORA_OP_FWD, lm.LORA_OP_BWD))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+
+    def step():
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], o["y"], o["u"], s, ws=ws)
+        lm.lora_linear_bwd(d["x"], d["W"], d["A"], d["B"], None, d["dy"], o["dx"], o["dA"], o["dB"], s, ws=ws)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for it in range(4):
+        _announce(f"narrow graph replay it={it}")
+        inp = lora_inputs(T, K, N, r, seed=61 + it)
+        for k in ("x", "W", "A", "B", "dy"):
+            d[k].copy_(inp[k])
+        for v in o.values():
+            v.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        compare({k: v.cpu() for k, v in o.items()}, oracle_lora(orc, inp, s), BF16, label=f"replay {it}")
+        step()  # eager calls between the replays
+        torch.cuda.synchronize()
