@@ -6,8 +6,11 @@
 
 namespace lora {
 
-// Dequantizing direct-to-LDS tiles (the shapes of the bf16 path; 256 x 128
-// and 128 x 64 choices run 128 x 128 tiles).
+// Dequantizing direct-to-LDS tiles (the shapes of the bf16 path; 128 x 64 and
+// row-major 256 x 128 choices run 128 x 128 tiles).  k-major 256 x 128 tiles
+// take 32-deep stages, whose code slots fit beside the ring: the INT4 dx of a
+// 3072 -> 8192 linear at 2048 tokens, 192 of them in one round against 384
+// tiles of 128 x 128 in one and a half, made its step 277 instead of 293 us.
 template <int QB>
 static hipError_t launch_q_dma(const GemmArgs &g, int shape, bool kmaj, const SideArgs *side, hipStream_t st) {
   if (kmaj) {
@@ -16,6 +19,8 @@ static hipError_t launch_q_dma(const GemmArgs &g, int shape, bool kmaj, const Si
         return launch_cfg<BF16, 256, 256, 2, 2, 1, B_KMAJ_TR, 64, 3, 3, 2, QB, EPI_STORE, 1>(g, side, st);
       case 4:
         return launch_cfg<BF16, 256, 192, 2, 2, 1, B_KMAJ_TR, 64, 3, 3, 2, QB, EPI_STORE, 1>(g, side, st);
+      case 1:
+        return launch_cfg<BF16, 256, 128, 4, 2, 1, B_KMAJ_TR, 64, 3, 3, 2, QB, EPI_STORE, 1>(g, side, st);
       default:
         return launch_cfg<BF16, 128, 128, 2, 2, 2, B_KMAJ_TR, 128, 3, 3, 2, QB, EPI_STORE, 1>(g, side, st);
     }
@@ -45,7 +50,7 @@ bool gemm_q_direct(const GemmArgs &g, int bits, bool b_kmajor, bool with_side) {
   // row), the LoRA stages within the first three, and the scales (and, for
   // k-major B, the codes of all K rows) within 32-bit offsets.
   const int shape = pick_shape(g.M, g.N, b_kmajor, with_side);
-  const int bke = shape == 2 || shape == 4 ? 32 : 64;
+  const int bke = shape == 2 || shape == 4 || (shape == 1 && b_kmajor) ? 32 : 64;
   const int64_t rowbytes = g.ldb * bits / 8, ldg = g.ldb >> g.qlog2g;
   const int64_t wrows = b_kmajor ? g.K : g.N;
   return (bits == 4 || bits == 8) && g.qlog2g >= 6 && g.r <= 3 * bke && wrows * ldg * 4 < (int64_t(1) << 31) &&

@@ -143,3 +143,14 @@ def test_quant_deterministic(orc):
     b = gpu_lora_q(inp, Wq, 2.0)
     for k in a:
         assert torch.equal(a[k], b[k]), k
+
+
+# Sizes whose dx runs 256 x 128 dequantizing tiles (ragged rows and columns, a
+# reduction that ends inside a stage, ranks in one and two LoRA stages), checked
+# on sampled rows of y and dx, dA and dB in full.
+@pytest.mark.parametrize("shape", [(1990, 3008, 264, 16, 4, 64), (2048, 3072, 520, 64, 8, 128)])
+def test_quant_dx_256x128_tiles(orc, shape):
+    T, K, N, r, bits, group = shape
+    p = lm.lora_linear_plan(T, K, N, r)
+    assert (p["bwd_tile_m"], p["bwd_tile_n"]) == (256, 128)
+    _qcase(orc, T, K, N, r, bits, group, seed=T + K, rows=sample_rows(T, 64))
