@@ -306,6 +306,11 @@ lora_status_t lora_ckpt_backward(const lora_node_t *nodes, int n, int64_t T, con
  * du = s dy B are computed; and over how many consecutive token ranges each
  * output block of the token reductions dA = du^T x and dB = s dy^T u runs
  * in the unfused dx launch (bwd_side_parts; 1 = all T in one workgroup).
+ * This is the tiled kernels' configuration.  Calls of up to 64 tokens (up to
+ * 128 where d_in x d_out >= 2^22), bf16, r a multiple of 4 up to 64 (32 above
+ * 32 tokens), given the workspace that lora_linear_workspace_bytes reports,
+ * run the few-token kernel instead: tiles of 32 x 64 with the rank-r pass in
+ * them, the reduction in up to four parts.
  * Errors as for the entry points' size checks. */
 typedef struct {
   int fwd_tile_m, fwd_tile_n, fwd_fused, fwd_u_parts;

@@ -350,11 +350,11 @@ TopkLayout topk_layout(int64_t V, int64_t k, bool paired) {
   L.total = off;
   return L;
 }
-// The paired build does half the products of the batched one on 256 x 256
-// tiles (155 against 70 ms at V = 128256, D = 3072, k = 1000).  Below one
+// The paired build does half the products of the batched one, on 256 x 128
+// tiles (158 against 92 ms at V = 128256, D = 3072, k = 1000).  Below one
 // block its single round is V / 256 tiles squared, halved, on 256 CUs, and
 // the 128 x 128 tiles of the batched build fill the chip as well or better.
-// Its lists take 57 KB a row; above 32 GiB the batched build's fixed amount is
+// Its lists take up to 64 KB a row; above 32 GiB the batched build's fixed amount is
 // taken instead.
 bool topk_paired(int64_t V, int64_t k) {
   return V >= TOPK_BLOCK && topk_layout(V, k, true).total <= (size_t(32) << 30);
