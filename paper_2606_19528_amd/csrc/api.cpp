@@ -412,7 +412,7 @@ hipError_t run_gemm(const GemmArgs &g, Dtype d, const QWeight *q, bool kmajor, c
 }
 
 // Whether the caller's workspace serves the narrow kernel: large enough,
-// aligned and clear of the operands (else the tiled kernels judge it).
+// aligned and clear of the operands (else the tiled kernels take the call or refuse it).
 bool narrow_fits(const NarrowWs &nw, void *ws, size_t ws_bytes, const std::vector<Range> &operands) {
   if (!nw.p.ok) return false;
   if (nw.total == 0) return true;

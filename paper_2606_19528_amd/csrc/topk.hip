@@ -1,10 +1,12 @@
 // topk.hip -- the top-k cosine-similarity table of the embedding matrix
 // (each token's k nearest tokens, the lookup table of the reduced-vocabulary
 // softmax), built without ever storing the V x V similarities:
-//   * the similarity GEMM runs over a batch of rows and one chunk of columns
-//     at a time; its epilogue (gemm.hip, EPI_TOPK) appends to each row's
-//     candidate list every cosine above the row's current threshold;
-//   * after each chunk, topk_select_kernel keeps the k best candidates of
+//   * the similarity GEMM runs over rounds of block pairs, each product serving
+//     both of its rows (EPI_TOPK_PAIRS in gemm_kernel.hpp), or with a smaller
+//     workspace over a batch of rows and one chunk of columns at a time
+//     (EPI_TOPK); its epilogue appends to a row's candidate list every cosine
+//     above the row's current threshold;
+//   * after each round or chunk, topk_select_kernel keeps the k best candidates of
 //     each row whose list might not hold another chunk (exact radix select on
 //     64-bit keys: similarity, then the smaller token index) and raises its
 //     threshold to the k-th best; with lists much longer than k + one chunk
