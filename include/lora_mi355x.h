@@ -57,9 +57,9 @@
  * they cannot change a result: the counters of the fused hand-over (they
  * order work; see lora_handover_giveups); the part counts of the dA / dB
  * token reductions that run as token parts (they pick the part that adds
- * the parts' tiles, which it adds in ascending part order); and, in the
- * top-k table build, the reservation of candidate-list slots, whose order is
- * normalised by the selection (ties go to the smaller index).
+ * the parts' tiles, which it adds in ascending part order); the exchange that
+ * picks it in the few-token kernel; and, in the top-k table build, the
+ * reservation of candidate-list slots, whose order is normalised by the selection (ties go to the smaller index).
  *
  * Device memory held by the library itself: one 4-byte counter per device
  * (lora_handover_giveups); everything else is the caller's.
@@ -319,6 +319,19 @@ typedef struct {
 } lora_plan_t;
 lora_status_t lora_linear_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, lora_dtype_t dt,
                                lora_plan_t *plan);
+
+/* Whether calls of these sizes run the few-token kernel (`taken`) once they are
+ * given a workspace of fwd_bytes (bwd_bytes), its tiles of 32 tokens by 64
+ * columns of y (dx) and the parts of the reduction; and the workspace of the
+ * tiled kernels, which serves the call as well.  Host logic only; errors as for
+ * lora_linear_plan. */
+typedef struct {
+  int taken, tiles_m;
+  int fwd_tiles_n, fwd_parts, bwd_tiles_n, bwd_parts;
+  size_t fwd_bytes, bwd_bytes, fwd_tiled_bytes, bwd_tiled_bytes;
+} lora_few_token_plan_t;
+lora_status_t lora_few_token_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, lora_dtype_t dt,
+                                  lora_few_token_plan_t *plan);
 
 /* A fused launch hands the rank-r rows from its producer workgroups to its
  * tiles through counters in the workspace; a wait for them gives up after a

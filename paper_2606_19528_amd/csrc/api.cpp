@@ -260,7 +260,7 @@ NarrowWs narrow_ws(bool bwd, int64_t T, int64_t K, int64_t N, int64_t r, lora_dt
   size_t off = 0;
   L.sync = off;
   const bool meets = L.p.parts > 1 || pu.parts > 1 || (bwd && r > 0 && L.p.tiles_m > 1);
-  off += meets ? round256((size_t)std::max(L.p.flags, pu.flags) * 4) : 0;
+  off += meets ? round256((size_t)std::max(L.p.flags, pu.flags) * sizeof(meet_word)) : 0;
   L.slots = off;
   off += round256(std::max(L.p.slot_bytes, pu.slot_bytes));
   L.da = off;
@@ -477,7 +477,7 @@ lora_status_t fwd_impl(const void *x, const void *W, const void *qc, const float
     NarrowArgs a{};
     a.X = x; a.W = W; a.V = A; a.P = B; a.out = y; a.u_out = r > 0 ? u_save : nullptr;
     a.T = (int)T; a.N = (int)d_out; a.K = (int)d_in; a.r = (int)r; a.scale = scale;
-    a.sync = (unsigned *)(wsb + nw.sync);
+    a.sync = (meet_word *)(wsb + nw.sync);
     a.slots = (float *)(wsb + nw.slots);
     a.gen = next_gen();
     Timed t(K_GEMM_FWD, st);
@@ -607,7 +607,7 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
     char *wsb = (char *)ws;
     NarrowArgs a{};
     a.T = (int)T; a.r = (int)r; a.scale = scale;
-    a.sync = (unsigned *)(wsb + nw.sync);
+    a.sync = (meet_word *)(wsb + nw.sync);
     a.slots = (float *)(wsb + nw.slots);
     a.da_slots = (float *)(wsb + nw.da);
     const float *u = u_saved;
@@ -1108,6 +1108,29 @@ lora_status_t lora_linear_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r
     p.bwd_fused = B.fused;
     p.bwd_du_parts = B.sp_du.nsplit;
     p.bwd_side_parts = B.tparts;
+  }
+  *plan = p;
+  return LORA_OK;
+}
+
+lora_status_t lora_few_token_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, lora_dtype_t dt,
+                                  lora_few_token_plan_t *plan) {
+  if (!plan) return fail(LORA_EINVAL, "plan is NULL");
+  lora_status_t s = check_shapes(T, d_in, d_out, r, dt);
+  if (s != LORA_OK) return s;
+  const NarrowWs f = narrow_ws(false, T, d_in, d_out, r, dt), b = narrow_ws(true, T, d_in, d_out, r, dt);
+  lora_few_token_plan_t p{};
+  p.fwd_tiled_bytes = fwd_layout(T, d_in, d_out, r, dt).total;
+  p.bwd_tiled_bytes = bwd_layout(T, d_in, d_out, r, dt).total;
+  p.taken = f.p.ok && b.p.ok;
+  if (p.taken) {
+    p.tiles_m = f.p.tiles_m;
+    p.fwd_tiles_n = f.p.tiles_n;
+    p.fwd_parts = f.p.parts;
+    p.bwd_tiles_n = b.p.tiles_n;
+    p.bwd_parts = b.p.parts;
+    p.fwd_bytes = f.total;
+    p.bwd_bytes = b.total;
   }
   *plan = p;
   return LORA_OK;

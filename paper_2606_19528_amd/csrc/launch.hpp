@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "meet.hpp"
+
 namespace lora {
 
 enum Dtype { DT_BF16 = 0, DT_F32 = 1 };
@@ -341,9 +343,9 @@ struct NarrowArgs {
   const float *u_in;
   float *dA, *dB;
   // workspace: flags of the meetings, the parts' sums, the row tiles' dA
-  unsigned *sync;
+  meet_word *sync;
   float *slots, *da_slots;
-  unsigned gen;  // this launch's tag, never 0
+  meet_word gen;  // this launch's tag, never 0
   int tiles_m, tiles_n, parts, part_k;  // set by launch_narrow
 };
 struct NarrowPlan {

@@ -14,7 +14,7 @@
 //             dB = s dy^T u on further workgroups of the launch
 // A tile's parts meet in the workspace: each stores its fp32 sums (16-byte
 // stores at device scope), waits until they have completed and raises a flag;
-// the part that sees all flags adds all the sums in ascending order and
+// one part that sees all flags up adds all the sums in ascending order and
 // finishes the tile.  The same meeting joins the row tiles' shares of dA.  So
 // results do not depend on the order of arrival.
 //
@@ -25,6 +25,7 @@
 
 #include "kernels.hpp"
 #include "launch.hpp"
+#include "meet.hpp"
 
 namespace lora {
 
@@ -38,23 +39,27 @@ struct NwIC {
   static constexpr int value = V;
 };
 
-// One wave's part in a meeting of n <= 64 workgroups (its stores complete): it
-// raises its flag, the launch's tag, and once that store has completed looks
-// at all of them.  True when all are up: every workgroup's stores had completed
-// before its own flag rose, and of two that rise last, the later one's look
-// follows both, so at least one sees all.  More than one may: each then adds
-// the same values in the same order and stores the same results.  A workgroup
-// that sees all lowers them (0 is no launch's tag) for a replay with the same
-// tag; one that looks after that takes no further part.  (A counter instead
-// of flags serialised the arrivals, 1.1 us each.)
-__device__ __forceinline__ bool nw_meet(unsigned *flags, int mine, int n, unsigned gen, int lane) {
-  if (lane == 0) __hip_atomic_store(flags + mine, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  const unsigned f = lane < n ? __hip_atomic_load(flags + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : gen;
-  if (__ballot(f != gen)) return false;
-  if (lane < n) __hip_atomic_store(flags + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return true;
-}
+// The flags of a meeting of n <= 64 workgroups (meet.hpp) as one wave reads and
+// writes them, a word a lane.  (A counter instead of flags serialised the
+// arrivals, 1.1 us each; only those that see all flags up meet in the exchange.)
+struct NwFlags {
+  meet_word *w;
+  int lane;
+  __device__ void raise(int i, meet_word tag) {
+    if (lane == 0) __hip_atomic_store(w + i, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ void settle() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+  __device__ bool all_up(int n, meet_word tag) {
+    const meet_word f = lane < n ? __hip_atomic_load(w + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+    return __ballot(f != tag) == 0;
+  }
+  // (the return value is lane 0's)
+  __device__ meet_word lower(int n) {
+    if (lane == 0) return __hip_atomic_exchange(w, meet_word(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < n) __hip_atomic_store(w + lane, meet_word(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return 0;
+  }
+};
 
 // 16 bytes at device scope (sc1: past the caches that other XCDs do not see).
 constexpr int NW_SC1 = 16;
@@ -404,21 +409,25 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   }
 
   // ---- the parts meet ---------------------------------------------------------------
-  // (PL is free: its first word passes the outcome of a meeting)
-  volatile int *s_last = (volatile int *)PL;
+  // (PL is free: its first words pass the outcomes.  The exchange that picks the
+  // one that finishes runs beside the loads of the sums.)
+  volatile int *s_all = (volatile int *)PL, *s_mine = s_all + 1;
   if (a.parts > 1) {
     __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0): this wave's stores have completed
     __syncthreads();
+    NwFlags flags{a.sync + tile_id * a.parts, lane};
     if (wv == 0) {
-      const bool all = nw_meet(a.sync + tile_id * a.parts, part, a.parts, a.gen, lane);
-      if (lane == 0) *s_last = all;
+      const bool all = meet_arrive(flags, part, a.parts, a.gen);
+      if (lane == 0) *s_all = all;
     }
     __syncthreads();
-    if (!*s_last) return;
+    if (!*s_all) return;
     constexpr int Q = (BM * C / 4 + NT - 1) / NT;  // quads per thread
     f32x4 v[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) v[q] = nw_load(rsS, (tid + q * NT) * 16);
+    meet_word word0 = 0;
+    if (wv == 0) word0 = meet_lower(flags, a.parts);
     // (G parts' loads in flight; past the last part they read zeros)
     constexpr int G = Q <= 4 ? 4 : Q <= 8 ? 2 : 1;
     for (int p = 1; p < a.parts; p += G) {
@@ -438,7 +447,9 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
       const int e = tid + q * NT;
       if ((BM * C / 4) % NT == 0 || e < BM * C / 4) *(f32x4 *)(F + e / (C / 4) * LDF + e % (C / 4) * 4) = v[q];
     }
+    if (tid == 0) *s_mine = word0 == a.gen;
     __syncthreads();
+    if (!*s_mine) return;
   }
 
   // ---- the finished tile: u, the LoRA step, the output ------------------------------
@@ -515,13 +526,15 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
     if (a.tiles_m > 1) {
       __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
       __syncthreads();
+      // (Two may see all: they store the same sums, and raise nothing after.)
       if (wv == 0) {
-        const bool all = nw_meet(a.sync + (int64_t)a.tiles_n * a.tiles_m * a.parts + nt * a.tiles_m, mt, a.tiles_m, a.gen,
-                                 lane);
-        if (lane == 0) *s_last = all;
+        NwFlags flags{a.sync + (int64_t)a.tiles_n * a.tiles_m * a.parts + nt * a.tiles_m, lane};
+        const bool all = meet_arrive(flags, mt, a.tiles_m, a.gen);
+        if (all) meet_lower(flags, a.tiles_m);
+        if (lane == 0) *s_all = all;
       }
       __syncthreads();
-      if (!*s_last) return;
+      if (!*s_all) return;
       for (int e = tid; e < r * (BN / 4); e += NT) {
         const int j = e / (BN / 4), lc = e % (BN / 4) * 4;
         f32x4 v = nw_load(rsD, (j * BN + lc) * 4);

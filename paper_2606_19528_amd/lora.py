@@ -34,6 +34,13 @@ class _Plan(ctypes.Structure):
                                              "bwd_side_parts")]
 
 
+class _FewTokenPlan(ctypes.Structure):
+    """lora_few_token_plan_t of the C ABI."""
+    _fields_ = [(n, ctypes.c_int) for n in ("taken", "tiles_m", "fwd_tiles_n", "fwd_parts", "bwd_tiles_n",
+                                            "bwd_parts")]
+    _fields_ += [(n, ctypes.c_size_t) for n in ("fwd_bytes", "bwd_bytes", "fwd_tiled_bytes", "bwd_tiled_bytes")]
+
+
 class LoraError(RuntimeError):
     def __init__(self, status: int, where: str, detail: str):
         super().__init__(f"{where}: status {status} ({detail})")
@@ -112,6 +119,8 @@ def lib() -> ctypes.CDLL:
     L.lora_kernel_count.restype = i32
     L.lora_linear_plan.argtypes = [i64, i64, i64, i64, i32, ctypes.POINTER(_Plan)]
     L.lora_linear_plan.restype = i32
+    L.lora_few_token_plan.argtypes = [i64, i64, i64, i64, i32, ctypes.POINTER(_FewTokenPlan)]
+    L.lora_few_token_plan.restype = i32
     L.lora_handover_giveups.argtypes = [ctypes.POINTER(ctypes.c_uint64), i32]
     L.lora_handover_giveups.restype = i32
     L.lora_debug_set_handover.argtypes = [i32]
@@ -445,6 +454,14 @@ def lora_linear_plan(T: int, d_in: int, d_out: int, r: int, dt: int = LORA_BF16)
     p = _Plan()
     _check(lib().lora_linear_plan(T, d_in, d_out, r, dt, ctypes.byref(p)), "lora_linear_plan")
     return {n: getattr(p, n) for n, _ in _Plan._fields_}
+
+
+def lora_few_token_plan(T: int, d_in: int, d_out: int, r: int, dt: int = LORA_BF16) -> dict:
+    """Whether the few-token kernel takes calls of these sizes, its tiles and parts,
+    and the workspaces that it and the tiled kernels want."""
+    p = _FewTokenPlan()
+    _check(lib().lora_few_token_plan(T, d_in, d_out, r, dt, ctypes.byref(p)), "lora_few_token_plan")
+    return {n: getattr(p, n) for n, _ in _FewTokenPlan._fields_}
 
 
 def handover_giveups(reset: bool = False) -> int:

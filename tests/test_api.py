@@ -363,6 +363,23 @@ def test_plan_query():
     assert lib.lora_linear_plan(64, 128, 128, 8, 0, None) == EINVAL
 
 
+def test_few_token_plan_query():
+    p = lm.lora_few_token_plan(64, 2048, 2048, 16)
+    assert (p["taken"], p["tiles_m"], p["fwd_tiles_n"], p["fwd_parts"], p["bwd_parts"]) == (1, 2, 32, 2, 2)
+    for op, name in ((lm.LORA_OP_FWD, "fwd"), (lm.LORA_OP_BWD, "bwd")):
+        n = lm.lora_linear_workspace_bytes(op, 64, 2048, 2048, 16, lm.LORA_BF16)
+        assert n == max(p[name + "_bytes"], p[name + "_tiled_bytes"])
+    # refused: many tokens, many over a small W or a wide rank, other types, ranks not in fours
+    for T, K, N, r, dt in ((129, 2048, 2048, 16, 0), (65, 1024, 1024, 16, 0), (33, 2048, 2048, 36, 0),
+                           (24, 2048, 2048, 16, 1), (24, 2048, 2048, 6, 0), (24, 2048, 2048, 68, 0)):
+        assert lm.lora_few_token_plan(T, K, N, r, dt)["taken"] == 0, (T, K, N, r, dt)
+    lib = lm.lib()
+    plan = L._FewTokenPlan()
+    assert lib.lora_few_token_plan(0, 128, 128, 8, 0, ctypes.byref(plan)) == EINVAL
+    assert lib.lora_few_token_plan(64, 100, 128, 8, 0, ctypes.byref(plan)) == EUNSUP
+    assert lib.lora_few_token_plan(64, 128, 128, 8, 0, None) == EINVAL
+
+
 def test_handover_hooks_reject_bad_arguments():
     lib = lm.lib()
     assert lib.lora_debug_set_handover(-1) == EINVAL

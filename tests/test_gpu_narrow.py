@@ -14,6 +14,7 @@ from workloads import lora_inputs
 
 pytestmark = pytest.mark.gpu
 BF16 = torch.bfloat16
+FLAG_WORDS = 1  # 32-bit words of a meeting's flag, the workspace's first contents
 
 
 def _announce(msg):
@@ -144,3 +145,53 @@ def test_narrow_graph_replay(orc):
         compare({k: v.cpu() for k, v in o.items()}, oracle_lora(orc, inp, s), BF16, label=f"replay {it}")
         step()  # eager calls between the replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("shape", [(64, 2048, 2048, 16), (50, 1024, 3072, 16), (40, 2048, 11008, 16),
+                                   (128, 1024, 4096, 16)], ids=lambda s: "x".join(map(str, s)))
+def test_narrow_replays_with_parts_and_row_tiles(shape):
+    """Replays (one tag) of a step whose tiles' parts meet and whose row tiles then
+    meet over dA: each replay equals the eager call on its inputs bitwise, and
+    leaves every flag down."""
+    T, K, N, r = shape
+    _announce(f"narrow replays T={T} K={K} N={N} r={r}")
+    p = lm.lora_few_token_plan(T, K, N, r)
+    assert p["taken"] and p["bwd_parts"] > 1 and p["tiles_m"] > 1
+    inputs = [{k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=70 + i).items()} for i in range(3)]
+    d = {k: torch.empty_like(v) for k, v in inputs[0].items()}
+
+    def outputs():
+        return {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
+                "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
+                "dB": torch.empty(N, r, device="cuda")}
+
+    def step(d, o, wf=None, wb=None):
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], o["y"], o["u"], 2.0, ws=wf)
+        lm.lora_linear_bwd(d["x"], d["W"], d["A"], d["B"], o["u"], d["dy"], o["dx"], o["dA"], o["dB"], 2.0, ws=wb)
+
+    want = []
+    for i in inputs:
+        want.append(outputs())
+        step(i, want[-1])
+    o = outputs()
+    wf = torch.full((max(p["fwd_bytes"], p["fwd_tiled_bytes"]),), 0xFF, dtype=torch.uint8, device="cuda")
+    wb = torch.full((max(p["bwd_bytes"], p["bwd_tiled_bytes"]),), 0xFF, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(d, o, wf, wb)
+    tiles = p["tiles_m"] * p["bwd_tiles_n"]
+    for it in range(30):
+        for k in d:
+            d[k].copy_(inputs[it % 3][k])
+        for v in o.values():
+            v.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in o:
+            assert torch.equal(o[k], want[it % 3][k]), (it, k)
+        flags = wb.view(torch.int32)[: tiles * (p["bwd_parts"] + 1) * FLAG_WORDS]
+        assert int(flags.count_nonzero()) == 0, it
+        if p["fwd_parts"] > 1:
+            flags = wf.view(torch.int32)[: p["tiles_m"] * p["fwd_tiles_n"] * p["fwd_parts"] * FLAG_WORDS]
+            assert int(flags.count_nonzero()) == 0, it
