@@ -59,7 +59,8 @@
  * token reductions that run as token parts (they pick the part that adds
  * the parts' tiles, which it adds in ascending part order); the exchange that
  * picks it in the few-token kernel; and, in the top-k table build, the
- * reservation of candidate-list slots, whose order is normalised by the selection (ties go to the smaller index).
+ * reservation of candidate-list slots, whose order is normalised by the
+ * selection (ties go to the smaller index).
  *
  * Device memory held by the library itself: one 4-byte counter per device
  * (lora_handover_giveups); everything else is the caller's.

@@ -151,6 +151,11 @@ unsigned int next_gen() {
   } while (v == 0);
   return v;
 }
+// Tag of a few-token launch's meetings.
+meet_word next_tag() {
+  static MeetTags tags;
+  return tags.take();
+}
 // Test hook (lora_debug_set_handover): 1 makes every tile's hand-over wait
 // of the following fused launches give up.
 std::atomic<int> g_fz_hold{0};
@@ -479,7 +484,7 @@ lora_status_t fwd_impl(const void *x, const void *W, const void *qc, const float
     a.T = (int)T; a.N = (int)d_out; a.K = (int)d_in; a.r = (int)r; a.scale = scale;
     a.sync = (meet_word *)(wsb + nw.sync);
     a.slots = (float *)(wsb + nw.slots);
-    a.gen = next_gen();
+    a.gen = next_tag();
     Timed t(K_GEMM_FWD, st);
     const hipError_t e = launch_narrow(a, nw.p, false, st);
     t.done();
@@ -618,7 +623,7 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
       b.X = x; b.W = W; b.V = A; b.P = B;
       b.N = 0; b.K = (int)d_in;
       b.u_out = (float *)(wsb + nw.u);
-      b.gen = next_gen();
+      b.gen = next_tag();
       Timed t(K_LORA_DOWN, st);
       e = launch_narrow(b, pu, false, st);
       t.done();
@@ -628,7 +633,7 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
     a.X = dy; a.W = W; a.V = B; a.P = A; a.out = dx;
     a.N = (int)d_in; a.K = (int)d_out;
     a.xin = x; a.u_in = u; a.dA = dA; a.dB = dB;
-    a.gen = next_gen();
+    a.gen = next_tag();
     Timed t(K_GEMM_BWD_DX, st);
     e = launch_narrow(a, nw.p, true, st);
     t.done();

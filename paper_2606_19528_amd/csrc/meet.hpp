@@ -10,13 +10,46 @@
 //   F::all_up(n, tag)   reads all n words; true when each is the tag
 //   F::lower(n)         word 0 is exchanged with 0, the others set to 0;
 //                       returns what word 0 held
+//
+// Nothing sets the words ahead of the launch: they hold whatever the workspace
+// held.  So a tag is a word that no data is: its upper half is a NaN as fp32, as
+// a pair of bf16 and, with the lower, as fp64, and no index or count; and its
+// payload of 52 bits starts from a number of the system's random source, so that
+// data made to look like a tag is not one.
 #pragma once
 
+#include <sys/random.h>
+
+#include <atomic>
+#include <chrono>
 #include <cstdint>
 
 namespace lora {
 
-using meet_word = uint32_t;
+using meet_word = uint64_t;
+
+// Tags of a process's launches, never 0 and never the same twice (2^52 of them).
+class MeetTags {
+ public:
+  MeetTags() : next_(start()) {}
+  meet_word take() {
+    uint64_t payload;
+    do {
+      payload = next_.fetch_add(1, std::memory_order_relaxed) & (BITS - 1);
+    } while (payload == 0);  // (that word is an infinity, not a NaN)
+    return 0x7FF0000000000000ull | payload;
+  }
+
+ private:
+  static constexpr uint64_t BITS = uint64_t(1) << 52;
+  static uint64_t start() {
+    uint64_t v = 0;
+    if (getentropy(&v, sizeof v) == 0) return v;
+    // (no random source: the time in ns, spread over the word by an odd factor)
+    return (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull;
+  }
+  std::atomic<uint64_t> next_;
+};
 
 // Workgroup `mine` arrives, its share complete in memory.  True when it sees
 // every flag up: every workgroup's share was complete before its own flag

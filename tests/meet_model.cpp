@@ -2,7 +2,7 @@
 // memory whose every access is one step, taken in every order that the
 // workgroups of a launch allow.
 //
-//   meet_model <tiles> <parts> <launches> <variant>
+//   meet_model <tiles> <parts> <launches> <variant> <tag>
 //
 // `tiles` row tiles of `parts` workgroups each: the parts of a tile meet, the one
 // that finishes the tile stores the tile's share and meets the other tiles'.
@@ -14,6 +14,15 @@
 // flags goes on and a tile may be finished twice, with the same values (a
 // mistake that the model has to find: the second to finish raises the tile's
 // flag again).
+// tag: "taken", one of MeetTags; "counted", a small number (a mistake again).
+// The flags start as the whole numbers 1, 2, 3, ..., and so do they once more as
+// pairs of 32 bits.
+//
+//   meet_model tags <count>
+//
+// prints the first and exits 1 if one of `count` tags is a word that ordinary
+// data holds: a half or the whole below 2^30 as an integer, or a finite fp64.
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -69,7 +78,7 @@ struct Flags {
 
 int tiles, parts;
 bool claim;
-constexpr meet_word TAG = 77;
+meet_word TAG;
 
 // memory: flags of the tiles, flags of the last meeting, shares, counts
 int at_flags(int tile) { return tile * parts; }
@@ -129,14 +138,32 @@ int fail(const char *what, Word launch) {
 }  // namespace
 
 int main(int argc, char **argv) {
-  if (argc != 5) return 2;
+  lora::MeetTags tags;
+  if (argc == 3 && !std::strcmp(argv[1], "tags")) {
+    meet_word last = 0;
+    for (int i = 0, n = std::atoi(argv[2]); i < n; ++i) {
+      const meet_word t = tags.take();
+      if (i == 0) std::printf("%llu\n", (unsigned long long)t);
+      double d;
+      std::memcpy(&d, &t, sizeof d);
+      if (t >> 32 < 1u << 30 || !std::isnan(d) || t == last) return 1;
+      last = t;
+    }
+    return 0;
+  }
+  if (argc != 6) return 2;
+  TAG = std::strcmp(argv[5], "counted") ? tags.take() : 2;
   tiles = std::atoi(argv[1]);
   parts = std::atoi(argv[2]);
   const int launches = std::atoi(argv[3]);
   claim = std::strcmp(argv[4], "all") != 0;
   const int groups = tiles * parts;
   size_t states = 0;
-  std::vector<std::vector<Word>> starts = {std::vector<Word>(words(), 0)};
+  std::vector<std::vector<Word>> starts(2, std::vector<Word>(words(), 0));
+  for (int w = 0; w < at_part(0, 0); ++w) {
+    starts[0][w] = w + 1;
+    starts[1][w] = (Word)(2 * w + 2) << 32 | (2 * w + 1);
+  }
   for (Word launch = 1; launch <= (Word)launches; ++launch) {
     std::unordered_set<std::string> seen;
     std::unordered_map<std::string, std::vector<Word>> ends;
@@ -173,7 +200,7 @@ int main(int argc, char **argv) {
             return fail("a tile was not finished exactly once", launch);
         if (!s.mem[at_end()]) return fail("nobody finished the last meeting", launch);
         for (int w = 0; w < at_part(0, 0); ++w)
-          if (s.mem[w]) return fail("a flag is still up", launch);
+          if (s.mem[w] == TAG) return fail("a flag is still up", launch);
         for (int w = at_finished(0); w < words(); ++w) s.mem[w] = 0;
         ends.emplace(std::string((const char *)s.mem.data(), s.mem.size() * sizeof(Word)), s.mem);
         continue;

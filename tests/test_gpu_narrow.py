@@ -14,7 +14,7 @@ from workloads import lora_inputs
 
 pytestmark = pytest.mark.gpu
 BF16 = torch.bfloat16
-FLAG_WORDS = 1  # 32-bit words of a meeting's flag, the workspace's first contents
+FLAG_WORDS = 2  # 32-bit words of a meeting's flag, the workspace's first contents
 
 
 def _announce(msg):
@@ -195,3 +195,46 @@ def test_narrow_replays_with_parts_and_row_tiles(shape):
         if p["fwd_parts"] > 1:
             flags = wf.view(torch.int32)[: p["tiles_m"] * p["fwd_tiles_n"] * p["fwd_parts"] * FLAG_WORDS]
             assert int(flags.count_nonzero()) == 0, it
+
+
+@pytest.mark.parametrize("fill", ["int32", "int64", "ones", "fused call"])
+@pytest.mark.parametrize("shape", [(24, 3072, 3072, 16), (64, 2048, 2048, 16)], ids=lambda s: "x".join(map(str, s)))
+def test_narrow_over_data_of_other_calls(shape, fill):
+    """The workspace holds what a program leaves in memory: the whole numbers that
+    count its calls, ones, or the hand-over words and sums of a call of many
+    tokens.  Every result is that of a clean workspace, bitwise."""
+    T, K, N, r = shape
+    _announce(f"narrow over {fill} T={T}")
+    assert lm.lora_few_token_plan(T, K, N, r)["taken"]
+    many = {k: v.cuda() for k, v in lora_inputs(640, K, N, r, seed=80).items()}
+    d = {k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=81).items()}
+
+    def run(d, ws):
+        T = d["x"].shape[0]
+        o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
+             "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
+             "dB": torch.empty(N, r, device="cuda")}
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], o["y"], o["u"], 2.0, ws=ws)
+        if fill == "fused call" and T < 640:
+            run(many, ws)
+        lm.lora_linear_bwd(d["x"], d["W"], d["A"], d["B"], None, d["dy"], o["dx"], o["dA"], o["dB"], 2.0, ws=ws)
+        return o
+
+    n = max(lm.lora_linear_workspace_bytes(op, t, K, N, r, lm.LORA_BF16)
+            for t in (T, 640) for op in (lm.LORA_OP_FWD, lm.LORA_OP_BWD))
+    n = (n + 7) // 8 * 8
+    want = run(d, torch.zeros(n, dtype=torch.uint8, device="cuda"))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    for it in range(6):
+        if fill == "int32":
+            ws.view(torch.int32).copy_(torch.arange(n // 4, dtype=torch.int32))
+        elif fill == "int64":
+            ws.view(torch.int64).copy_(torch.arange(n // 8))
+        elif fill == "ones":
+            ws.view(torch.int32).fill_(1)
+        else:
+            run(many, ws)
+        got = run(d, ws)
+        torch.cuda.synchronize()
+        for k in want:
+            assert torch.equal(got[k], want[k]), (it, k)
