@@ -256,7 +256,8 @@ size_t topk_table_workspace_bytes(int64_t V, int64_t D, int64_t k);
  * rows at once and so computes each similarity once instead of twice (about
  * 57 KB a row; 7.4 GB at V = 128256, k = 1000); topk_table_workspace_bytes
  * where that build does not pay.  Any smaller workspace of at least
- * topk_table_workspace_bytes runs the build over batches of rows. */
+ * topk_table_workspace_bytes runs the build over batches of rows, with the same
+ * table and values bitwise. */
 size_t topk_table_workspace_bytes_paired(int64_t V, int64_t D, int64_t k);
 lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, int32_t *table,
                                float *values, void *ws, size_t ws_bytes, void *hip_stream);

@@ -870,8 +870,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
     for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
-  // DUAL: even and odd k-slices are summed apart and added at the end, the
-  // precision of a k-split between two waves.
+  // DUAL: the slices of even and of odd stages (32 deep) are summed apart and
+  // added at the end, as the two waves of the 128 x 128 tiles share their 64-deep
+  // stages: the same sums bitwise.
   constexpr bool DUAL = EPI == EPI_TOPK_PAIRS;
   f32x16 acc2[DUAL ? FM : 1][DUAL ? FN : 1];
   if constexpr (DUAL) {
@@ -1202,17 +1203,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
       for (int s2 = 0; s2 < SPW; ++s2) read_frags_d(BUF, s2, f[s2]);
     };
     auto mma_stage = [&](const Frag(&f)[SPW]) {
-      if constexpr (DUAL) {
-#pragma unroll
-        for (int s2 = 0; s2 < SPW; ++s2)
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) mma32(E(), (s2 % 2 ? acc2 : acc)[i][j], f[s2].b[j], f[s2].a[i]);
-        return;
-      }
 #pragma unroll
       for (int s2 = 0; s2 < SPW; ++s2) mma_frags(f[s2]);
+    };
+    auto mma_stage2 = [&](const Frag(&f)[SPW]) {  // into acc2
+#pragma unroll
+      for (int s2 = 0; s2 < SPW; ++s2)
+#pragma unroll
+        for (int i = 0; i < (DUAL ? FM : 0); ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) mma32(E(), acc2[i][j], f[s2].b[j], f[s2].a[i]);
     };
     if constexpr (QD) {
       // Quantized B.  Step kt: wait for its loads of stage kt + 1 and of the
@@ -1342,7 +1342,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
           static_for<ri * IPS / NRO, (ri + 1) * IPS / NRO>(
               [&](auto QI) { dma_one(IC<P % NBUF>(), kt + NBUF, QI, MASK); });
         });
-        mma_stage(F[P % 2]);
+        if constexpr (DUAL && P % 2) mma_stage2(F[P % 2]);
+        else mma_stage(F[P % 2]);
         constexpr int NM = SPW * FM * FN;
         constexpr int NR = SPW * (FM + FN * (BMODE == B_KMAJ_TR ? 2 : 1));
         static_for<0, NM>([&](auto MI) {
@@ -1679,9 +1680,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
     return;
   }
   if constexpr (EPI == EPI_TOPK_PAIRS) {
-    // Cosines c = z * rn[m] * rn[n] of this tile, each offered to row m's list
-    // and, the similarity being symmetric, to row n's (not in the tiles on
-    // the diagonal, which hold both orders of a pair).  Each wave works on its
+    // Cosines of this tile, each offered to row m's list and, the similarity
+    // being symmetric, to row n's (not in the tiles on the diagonal, which hold
+    // both orders of a pair): z * rn[m] * rn[n] to row m, z * rn[n] * rn[m] to
+    // row n.  The norm of the list's own row comes first, so that equal rows have
+    // equal similarities to a third whichever of them is the tile's row; the
+    // values are bitwise those of EPI_TOPK.  Each wave works on its
     // 64 x 64 block in registers.  Row role: a lane holds 32 columns of its
     // row per block row i and lane ^ 32 the other 32; one atomic add per row
     // of the wave reserves the slots.  Column role: the 32 lanes of a half
@@ -1717,7 +1721,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
           const float2 v = rt[BM + wc + j * 32 + 8 * (x / 4) + 4 * half + x % 4];
           tn[j][x] = v.y;
 #pragma unroll
-          for (int i = 0; i < FM; ++i) acc[i][j][x] = (acc[i][j][x] + acc2[i][j][x]) * ra[i] * v.x;
+          for (int i = 0; i < FM; ++i) {
+            const float z = acc[i][j][x] + acc2[i][j][x];
+            acc[i][j][x] = z * ra[i] * v.x;   // row role
+            acc2[i][j][x] = z * v.x * ra[i];  // column role
+          }
         }
     }
     // counts of both roles, then all the atomics, then the stores
@@ -1738,7 +1746,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
           int lo = 0, hi = 0;
 #pragma unroll
           for (int i = 0; i < FM; ++i) {
-            const uint64_t mk = __ballot(acc[i][j][x] >= tn[j][x]);
+            const uint64_t mk = __ballot(acc2[i][j][x] >= tn[j][x]);
             lo += __builtin_popcount((uint32_t)mk);
             hi += __builtin_popcount((uint32_t)(mk >> 32));
           }
@@ -1783,7 +1791,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
         uint64_t *kr = g.tk_key + (int64_t)(n0 + wc + c + 4 * half) * g.tk_cap;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
-          const float v = acc[i][j][x];
+          const float v = acc2[i][j][x];
           const bool in = v >= tn[j][x];
           const uint64_t mk = __ballot(in);
           if (mk == 0) continue;

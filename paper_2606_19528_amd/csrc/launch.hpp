@@ -126,7 +126,7 @@ struct GemmArgs {
 //   EPI_F32       C fp32 [M][ldc] (+)= A B (B k-major);
 //   EPI_TOPK      no C; candidates of the similarity table (B row-major).
 //   EPI_TOPK_PAIRS  the same for one round of block pairs, each product
-//                 serving both of its rows (256 x 256 tiles; launch_topk_round).
+//                 serving both of its rows (256 x 128 tiles; launch_topk_round).
 enum { EPI_STORE = 0, EPI_CE_STATS = 1, EPI_CE_DZ = 2, EPI_F32 = 3, EPI_TOPK = 4, EPI_TOPK_PAIRS = 5 };
 hipError_t launch_gemm_epi(const GemmArgs &g, int epi, hipStream_t st);
 

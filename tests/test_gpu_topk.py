@@ -95,8 +95,8 @@ def test_topk_table_paired_equals_batched(orc, V, D, k):
     """From one block of 4096 rows the build runs rounds of block pairs, each
     similarity serving both rows (one whole block, a ragged second block, an
     odd number of blocks with a bye); given only the smaller workspace it runs
-    row batches.  Both agree with the oracle and, up to near-ties, with each
-    other; rows repeated far apart tie exactly, the smaller index first."""
+    row batches.  Both agree with the oracle and bitwise with each other; rows
+    repeated far apart tie exactly, the smaller index first."""
     _announce(f"topk paired V={V} D={D} k={k}")
     W = _embeddings(V, D, seed=V)
     W[V - 1] = W[3]
@@ -111,8 +111,7 @@ def test_topk_table_paired_equals_batched(orc, V, D, k):
         lm.topk_table_build(Wd, k, table, values, ws=ws)
         torch.cuda.synchronize()
         out[name] = (table.cpu(), values.cpu())
-    # the tile shapes sum in different orders: at most a few roundings apart
-    assert (out["paired"][1] - out["batched"][1]).abs().max() <= EPS
+    assert torch.equal(out["paired"][0], out["batched"][0]) and torch.equal(out["paired"][1], out["batched"][1])
     for table, values in out.values():
         for i in (3, V // 2, V - 1):
             assert table[i, :3].tolist() == [3, V // 2, V - 1]
@@ -129,3 +128,40 @@ def test_topk_table_paired_all_equal():
     table = lm.topk_table_build(W, k)
     torch.cuda.synchronize()
     assert torch.equal(table.cpu(), torch.arange(k, dtype=torch.int32).repeat(V, 1))
+
+
+@pytest.mark.parametrize("k", [6, 7, 64])
+def test_topk_table_equal_rows_tie_for_every_query(k):
+    """Equal rows in different blocks have bitwise equal similarities to every
+    other token, whose norms vary over four decades, and stand in ascending order
+    of their index, also where k cuts between them."""
+    V, D = 12300, 64
+    _announce(f"topk equal rows k={k}")
+    W = _embeddings(V, D, seed=11).float()
+    W *= 10.0 ** (4.0 * torch.rand(V, 1, generator=torch.Generator().manual_seed(12)) - 2.0)
+    same = [7, 4099, 5000, 8191, 8193, 12299]
+    centre = W[7].clone()
+    near = list(range(100, 12000, 37))  # queries around the repeated row
+    W[near] = centre * (0.5 + torch.rand(len(near), 1, generator=torch.Generator().manual_seed(13))) + 0.4 * W[near] / W[
+        near].norm(dim=1, keepdim=True) * centre.norm()
+    W[same] = centre
+    W = W.to(torch.bfloat16)
+    out = []
+    for n in (lm.lib().topk_table_workspace_bytes_paired(V, D, k), lm.lib().topk_table_workspace_bytes(V, D, k)):
+        table = torch.empty(V, k, dtype=torch.int32, device="cuda")
+        values = torch.empty(V, k, dtype=torch.float32, device="cuda")
+        lm.topk_table_build(W.cuda(), k, table, values, ws=torch.empty(n, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        out.append((table.cpu(), values.cpu()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    table, values = out[0]
+    seen = 0
+    for i in range(V):
+        at = [(int(t), c) for c, t in enumerate(table[i].tolist()) if t in same]
+        if not at:
+            continue
+        seen += 1
+        assert [t for t, _ in at] == same[: len(at)], (i, at)
+        assert len({float(values[i, c]) for _, c in at}) == 1, i
+        assert len(at) == len(same) or at[-1][1] == k - 1, i  # none left out ahead of another token
+    assert seen > 200  # queries that the repeated rows reach
