@@ -352,6 +352,11 @@ lora_status_t lora_handover_giveups(uint64_t *count, int reset);
  * restores normal operation.  Errors: LORA_EINVAL for other values. */
 lora_status_t lora_debug_set_handover(int hold);
 
+/* Test hook: 1 when the host range [host, host + bytes) lies in one pinned
+ * allocation that the device maps, so that the checkpointed step's copy kernel
+ * may touch all of it; else 0 (the copies then go through hipMemcpyAsync). */
+int lora_debug_host_mapped(const void *host, size_t bytes);
+
 /* Static text for a status code. */
 const char *lora_status_str(lora_status_t status);
 

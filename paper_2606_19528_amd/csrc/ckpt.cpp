@@ -193,4 +193,8 @@ lora_status_t lora_ckpt_backward(const lora_node_t *nodes, int n, int64_t T, con
   return LORA_OK;
 }
 
+int lora_debug_host_mapped(const void *host, size_t bytes) {
+  return host && bytes > 0 && lora::host_copy_mapped(host, bytes) ? 1 : 0;
+}
+
 }  // extern "C"

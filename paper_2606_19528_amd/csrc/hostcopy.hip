@@ -35,18 +35,21 @@ __global__ __launch_bounds__(HC_NT) void host_copy_kernel(u32x4 *dst, const u32x
   }
 }
 
-// Device address of the host range [p, p + bytes) if all of it is one mapped
+// Device address of the host range [p, p + bytes) if all of it lies in one mapped
 // pinned allocation, else null (the error a failed lookup leaves is cleared).
 static char *mapped(const void *p, size_t bytes) {
-  void *lo = nullptr, *hi = nullptr;
-  char *h = (char *)const_cast<void *>(p);
-  if (hipHostGetDevicePointer(&lo, h, 0) != hipSuccess || hipHostGetDevicePointer(&hi, h + bytes - 1, 0) != hipSuccess ||
-      !lo || (char *)hi - (char *)lo != (ptrdiff_t)(bytes - 1)) {
+  void *dev = nullptr, *base = nullptr;
+  size_t size = 0;
+  if (hipHostGetDevicePointer(&dev, const_cast<void *>(p), 0) != hipSuccess || !dev ||
+      hipMemGetAddressRange((hipDeviceptr_t *)&base, &size, (hipDeviceptr_t)dev) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
-  return (char *)lo;
+  const size_t off = (size_t)((char *)dev - (char *)base);
+  return dev >= base && off <= size && bytes <= size - off ? (char *)dev : nullptr;
 }
+
+bool host_copy_mapped(const void *host, size_t bytes) { return mapped(host, bytes) != nullptr; }
 
 hipError_t launch_host_copy(void *dst, const void *src, size_t bytes, bool to_host, hipStream_t st) {
   if (bytes == 0) return hipSuccess;

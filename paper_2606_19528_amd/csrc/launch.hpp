@@ -192,6 +192,7 @@ hipError_t launch_dh_finish(const float *acc, const int32_t *rows, int nrows, in
 // copy kernel of hostcopy.hip for pinned memory in whole aligned 16-byte
 // vectors, hipMemcpyAsync otherwise.
 hipError_t launch_host_copy(void *dst, const void *src, size_t bytes, bool to_host, hipStream_t st);
+bool host_copy_mapped(const void *host, size_t bytes);  // whether [host, host + bytes) is such memory
 
 // GEMM launch; `side` (may be NULL) adds the token-reduction workgroups.
 hipError_t launch_gemm(const GemmArgs &g, Dtype dt, bool b_kmajor, const SideArgs *side,

@@ -121,6 +121,8 @@ def lib() -> ctypes.CDLL:
     L.lora_linear_plan.restype = i32
     L.lora_few_token_plan.argtypes = [i64, i64, i64, i64, i32, ctypes.POINTER(_FewTokenPlan)]
     L.lora_few_token_plan.restype = i32
+    L.lora_debug_host_mapped.argtypes = [vp, sz]
+    L.lora_debug_host_mapped.restype = i32
     L.lora_handover_giveups.argtypes = [ctypes.POINTER(ctypes.c_uint64), i32]
     L.lora_handover_giveups.restype = i32
     L.lora_debug_set_handover.argtypes = [i32]

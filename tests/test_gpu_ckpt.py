@@ -132,3 +132,19 @@ def test_ckpt_stash_copies(T, offset):
     y, grads, dx = _plain(nodes, x0, g)
     assert torch.equal(out, y) and torch.equal(dx0, dx)
     assert all(torch.equal(nd["dA"], a) and torch.equal(nd["dB"], b) for nd, (a, b) in zip(nodes, grads))
+
+
+def test_ckpt_copy_kernel_takes_one_pinned_allocation_only():
+    """A range is the copy kernel's when all of it lies in one pinned allocation, not
+    when its two ends do: what stands between two allocations need not be mapped.
+    (Queries only, no copy.)"""
+    _announce("ckpt host ranges")
+    n = 1 << 20  # (a whole block of the pinned allocator)
+    a, b = (torch.empty(n, dtype=torch.uint8, pin_memory=True) for _ in range(2))
+    lo, hi = sorted((a.data_ptr(), b.data_ptr()))
+    mapped = lm.lib().lora_debug_host_mapped
+    assert mapped(lo, n) == 1 and mapped(lo + 16, n - 16) == 1 and mapped(lo + n - 1, 1) == 1
+    assert mapped(lo, n + 16) == 0 and mapped(lo + 16, n) == 0
+    assert mapped(lo, hi + n - lo) == 0
+    assert mapped(torch.empty(n, dtype=torch.uint8).data_ptr(), n) == 0
+    assert mapped(lo, 0) == 0 and mapped(None, n) == 0
