@@ -91,7 +91,9 @@ typedef enum { LORA_OP_FWD = 0, LORA_OP_BWD = 1, LORA_OP_FROZEN_DX = 2 } lora_op
  * or not the optional u pointers are given.  Returns 0 when none is needed
  * and (size_t)-1 for sizes the entry point would reject.  Pure host logic.
  * Up to 128 tokens (bf16) it includes what the few-token kernel wants; a call
- * given less, but the tiled kernels' amount, runs those. */
+ * given less, but the tiled kernels' amount, runs those.  (The two sum in
+ * different orders: a recomputed u is bitwise the saved one when both
+ * directions are given what this reports.) */
 size_t lora_linear_workspace_bytes(lora_op_t op, int64_t T, int64_t d_in, int64_t d_out,
                                    int64_t r, lora_dtype_t dt);
 
@@ -272,7 +274,8 @@ lora_status_t topk_table_build(const void *W, int64_t V, int64_t D, int64_t k, i
  * backpropagates.  The loss node between the two (the paper's LM head) is
  * the caller's: it turns the forward's output x_n into g_n = dL/dx_n.
  * Device memory: two activation and two gradient buffers of the widest node
- * plus one LoRA workspace (lora_ckpt_workspace_bytes), whatever n is; host
+ * plus one LoRA workspace (lora_ckpt_workspace_bytes; up to 128 tokens less
+ * serves as well, see lora_linear_workspace_bytes), whatever n is; host
  * memory: every node's input (lora_ckpt_host_bytes), which must be pinned
  * (hipHostMalloc) for the copies to run asynchronously.  Both calls return
  * once their work is enqueued; the host stash may be read or reused only

@@ -41,7 +41,8 @@ struct Plan {
   int64_t maxd = 0;        // widest activation
   size_t act_bytes = 0;    // one activation / gradient buffer
   size_t op_ws = 0;        // workspace of the widest LoRA call
-  size_t total = 0;
+  size_t op_least = 0;     // the same where only the tiled kernels' amount is given
+  size_t total = 0, least = 0;
   std::vector<size_t> stash_off;  // host offset of each node's input
   size_t stash_bytes = 0;
 };
@@ -56,12 +57,16 @@ lora_status_t plan(const lora_node_t *nodes, int n, int64_t T, Plan *p) {
     const size_t bw = lora_linear_workspace_bytes(LORA_OP_BWD, T, nd.d_in, nd.d_out, nd.r, LORA_BF16);
     if (fw == (size_t)-1 || bw == (size_t)-1) return LORA_EUNSUPPORTED;
     p->op_ws = std::max({p->op_ws, fw, bw});
+    lora_few_token_plan_t few;
+    if (lora_few_token_plan(T, nd.d_in, nd.d_out, nd.r, LORA_BF16, &few) != LORA_OK) return LORA_EUNSUPPORTED;
+    p->op_least = std::max({p->op_least, few.fwd_tiled_bytes, few.bwd_tiled_bytes});
     p->maxd = std::max({p->maxd, nd.d_in, nd.d_out});
     p->stash_off[i] = p->stash_bytes;
     p->stash_bytes += (size_t)T * nd.d_in * 2;
   }
   p->act_bytes = ((size_t)T * p->maxd * 2 + 255) & ~size_t(255);
   p->total = 4 * p->act_bytes + ((p->op_ws + 255) & ~size_t(255));
+  p->least = 4 * p->act_bytes + ((p->op_least + 255) & ~size_t(255));
   return LORA_OK;
 }
 
@@ -88,8 +93,9 @@ lora_status_t check_common(const lora_node_t *nodes, int n, int64_t T, void *hos
       return fail(LORA_EINVAL, "each node needs W, and A, B, dA, dB when r > 0");
   }
   if (!host_stash || host_bytes < p->stash_bytes) return fail(LORA_EWORKSPACE, "host stash missing or too small");
-  if (!ws || ws_bytes < p->total) return fail(LORA_EWORKSPACE, "device workspace missing or too small");
+  if (!ws || ws_bytes < p->least) return fail(LORA_EWORKSPACE, "device workspace missing or too small");
   if ((reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return fail(LORA_EINVAL, "workspace not 256-byte aligned");
+  if (ws_bytes < p->total) p->op_ws = p->op_least;  // few tokens: the tiled kernels serve them too
   return LORA_OK;
 }
 

@@ -299,6 +299,22 @@ def test_ckpt_sizes_and_rejects():
     assert lib.lora_ckpt_forward(nodes, 3, 128, x0, out, stash, big, wsp, big, None, None) == EINVAL
 
 
+def test_ckpt_takes_the_tiled_workspace():
+    """Up to 128 tokens a workspace for the tiled kernels still serves the chain (a
+    missing g_n is found after the sizes)."""
+    lib = lm.lib()
+    dims = [1024, 3072, 1024]
+    nodes = _chain(dims, r=16)
+    for T in (16, 64):
+        plans = [lm.lora_few_token_plan(T, a, b, 16) for a, b in zip(dims, dims[1:])]
+        op = max(p[k] for p in plans for k in ("fwd_tiled_bytes", "bwd_tiled_bytes"))
+        least = 4 * T * 3072 * 2 + op
+        assert least < lib.lora_ckpt_workspace_bytes(nodes, 2, T)
+        args = (nodes, 2, T, None, P(2), P(3), 1 << 40, ctypes.c_void_p(P(4).value))
+        assert lib.lora_ckpt_backward(*args, least, None, None) == EINVAL
+        assert lib.lora_ckpt_backward(*args, least - 1, None, None) == EWS
+
+
 def test_topk_table_sizes_and_rejects():
     lib = lm.lib()
     w = lib.topk_table_workspace_bytes

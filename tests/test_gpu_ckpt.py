@@ -148,3 +148,28 @@ def test_ckpt_copy_kernel_takes_one_pinned_allocation_only():
     assert mapped(lo, hi + n - lo) == 0
     assert mapped(torch.empty(n, dtype=torch.uint8).data_ptr(), n) == 0
     assert mapped(lo, 0) == 0 and mapped(None, n) == 0
+
+
+@pytest.mark.parametrize("T", [16, 64])
+def test_ckpt_with_the_tiled_workspace(T):
+    """Few tokens with room for the tiled kernels only."""
+    dims, ranks = [1024, 3072, 1024], [16, 16]
+    _announce(f"ckpt tiled workspace T={T}")
+    nodes, x0, g = _chain_inputs(T, dims, ranks, seed=T)
+    ws_b, host_b = lm.lora_ckpt_sizes(nodes, T)
+    plans = [lm.lora_few_token_plan(T, a, b, r) for a, b, r in zip(dims, dims[1:], ranks)]
+    least = 4 * T * max(dims) * 2 + max(p[k] for p in plans for k in ("fwd_tiled_bytes", "bwd_tiled_bytes"))
+    assert least < ws_b
+    ws = torch.zeros(ws_b, dtype=torch.uint8, device="cuda")
+    stash = torch.empty(host_b, dtype=torch.uint8, pin_memory=True)
+    out = torch.empty(T, dims[-1], dtype=torch.bfloat16, device="cuda")
+    dx0 = torch.empty(T, dims[0], dtype=torch.bfloat16, device="cuda")
+    lm.lora_ckpt_forward(nodes, x0, out, stash, ws[:least])
+    lm.lora_ckpt_backward(nodes, g, dx0, stash, ws[:least])
+    torch.cuda.synchronize()
+    assert int(ws[least:].count_nonzero()) == 0
+    y, grads, dx = _plain(nodes, x0, g)
+    tol = TOL[torch.bfloat16]
+    assert relerr(out.double().cpu(), y.double().cpu()) <= tol and relerr(dx0.double().cpu(), dx.double().cpu()) <= tol
+    for nd, (a, b) in zip(nodes, grads):
+        assert relerr(nd["dA"].cpu(), a.cpu()) <= tol and relerr(nd["dB"].cpu(), b.cpu()) <= tol
