@@ -48,8 +48,13 @@ def skinny_asm(tmp_path_factory):
     return _asm(tmp_path_factory, "skinny.hip")
 
 
-def _kernels(asm):
-    names = re.findall(r"^(_ZN4lora11gemm_kernel[^:\s]+): ;", asm, re.M)
+@pytest.fixture(scope="module")
+def narrow_asm(tmp_path_factory):
+    return _asm(tmp_path_factory, "narrow.hip")
+
+
+def _kernels(asm, kernel="gemm_kernel"):
+    names = re.findall(r"^(_ZN4lora%d%s[^:\s]+): ;" % (len(kernel), kernel), asm, re.M)
     assert names
     for n in names:
         body = asm[asm.index(n + ": ;"):]
@@ -76,6 +81,18 @@ def test_direct_to_lds_loads_come_from_the_assembly(gemm_asm):
                 lines = [l.strip() for l in blk.strip().splitlines()]
                 assert lines[0].startswith("s_mov_b32 m0") and lines[1].startswith("s_nop 0"), (name, lines)
                 assert lines[2].startswith("buffer_load_dwordx4"), (name, lines)
+    assert n_dma > 0
+
+
+def test_few_token_kernel_loads_and_m0(narrow_asm):
+    """The same of the few-token kernel, which also must not spill."""
+    n_dma = 0
+    for name, body in _kernels(narrow_asm, "narrow_kernel"):
+        outside = re.sub(r";;#ASMSTART.*?;;#ASMEND", "", body, flags=re.S)
+        assert not re.search(r"\bm0\b", outside), name
+        assert not re.search(r"buffer_load_dword\S*\s.*\blds\b", outside), name
+        n_dma += len(re.findall(r"buffer_load_dwordx4\s.*\blds\b", body))
+        assert _resources(narrow_asm, name)["ScratchSize"] == 0, name
     assert n_dma > 0
 
 
@@ -112,8 +129,8 @@ def _sgpr_hazards(asm):
     return n, bad
 
 
-def test_no_vector_written_sgpr_feeds_a_direct_to_lds_load(gemm_asm, skinny_asm):
-    for asm in (gemm_asm, skinny_asm):
+def test_no_vector_written_sgpr_feeds_a_direct_to_lds_load(gemm_asm, skinny_asm, narrow_asm):
+    for asm in (gemm_asm, skinny_asm, narrow_asm):
         n, bad = _sgpr_hazards(asm)
         assert n > 0
         assert not bad, bad[:5]

@@ -137,9 +137,12 @@ def test_backward_side_items_on_producers(orc, shape, recompute):
     _announce(f"fused bwd side items T={T} K={K} N={N} r={r} recompute={recompute}")
     inp = lora_inputs(T, K, N, r, seed=95)
     d = {k: v.cuda() for k, v in inp.items()}
+    assert lm.lora_linear_plan(T, K, N, r)["bwd_fused"]
+    few = lm.lora_few_token_plan(T, K, N, r)  # (with the tiled kernels' workspace those run)
+    assert not few["taken"] or few["bwd_tiled_bytes"] < few["bwd_bytes"]
     ws = _ws(T, K, N, r)
     o = _buffers(T, K, N, r)
-    _step(d, o, s, ws, ws, recompute=recompute)
+    _step(d, o, s, ws, ws[: few["bwd_tiled_bytes"]], recompute=recompute)
     torch.cuda.synchronize()
     ref = oracle_lora(orc, inp, s)
     compare({k: v.cpu() for k, v in o.items()}, ref, torch.bfloat16, label="side items on producers")

@@ -1,8 +1,9 @@
-"""GPU tests of the few-token kernel (up to 128 tokens, bf16): tiles of 32 or 64
-rows by 64 or 128 columns, the reduction in one part or several that meet in the
-workspace, one or two blocks of 32 rank columns, one or several row tiles.
-Every result against the fp64 oracle (max relative error <= 2e-2 per tensor,
-the bf16 bound of the other parity tests)."""
+"""GPU tests of the few-token kernel (up to 128 tokens, bf16): tiles of 32 rows by
+64 columns, the reduction in one part or several that meet in the workspace, one
+or two blocks of 32 rank columns, one to four row tiles.  Each test asserts through
+lora_few_token_plan that its calls run that kernel (or, at the rule's edges and
+with the smaller workspace, the tiled ones).  Every result against the fp64 oracle
+(max relative error <= 2e-2 per tensor, the bf16 bound of the other parity tests)."""
 import sys
 
 import pytest
@@ -23,17 +24,34 @@ def _announce(msg):
 
 # (T, d_in, d_out, r): tile edges in T; reductions of less than a stage, a
 # ragged last stage, one part and many; ragged column tiles; ranks whose rows
-# are not whole 16-byte vectors, one and two rank blocks, none.
+# are not whole 16-byte vectors, one and two rank blocks, none; parts and row
+# tiles together in either direction, one to four row tiles.
 SHAPES = [(1, 8, 8, 4), (1, 3072, 3072, 16), (16, 264, 72, 8), (24, 3072, 1032, 16), (31, 72, 520, 12),
-          (32, 1024, 64, 32), (33, 776, 2056, 64), (48, 2056, 1032, 36), (63, 4096, 256, 4), (64, 256, 4104, 64),
-          (65, 3080, 136, 8), (100, 520, 3072, 40), (127, 2048, 2048, 16), (128, 1032, 1032, 32), (129, 3072, 520, 24),
-          (103, 1544, 2056, 16), (95, 264, 8200, 4), (128, 2048, 1024, 64), (97, 1024, 3072, 28), (40, 2056, 3080, 0),
-          (120, 1032, 2056, 0), (128, 64, 64, 8)]
+          (32, 1024, 64, 32), (63, 4096, 256, 4), (40, 2056, 3080, 0), (64, 256, 4104, 16),
+          (32, 2056, 1032, 36), (20, 520, 2056, 40), (32, 1032, 264, 64), (17, 4104, 72, 64),
+          (33, 776, 2056, 32), (64, 2048, 2048, 16), (50, 4104, 520, 24), (48, 520, 4104, 28),
+          (65, 8200, 520, 24), (80, 1032, 4096, 12), (96, 4104, 1032, 16), (95, 520, 8200, 4),
+          (100, 4104, 1024, 32), (103, 1024, 4104, 16), (120, 2056, 2056, 0), (127, 2048, 2056, 16),
+          (128, 1032, 4104, 32), (128, 8200, 520, 8)]
+# The rule's edges: one token, one rank index or one weight row too many.
+BEYOND = [(129, 3072, 2056, 24), (65, 3080, 136, 8), (128, 64, 64, 8), (128, 2048, 2040, 16), (33, 776, 2056, 36),
+          (64, 256, 4104, 64), (100, 520, 3072, 40), (128, 2048, 3072, 64), (24, 1024, 520, 68), (24, 1024, 520, 6)]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_narrow_shapes_cover_the_plans():
+    plans = [lm.lora_few_token_plan(*s) | {"r": s[3]} for s in SHAPES]
+    assert all(p["taken"] for p in plans)
+    assert not any(lm.lora_few_token_plan(*s)["taken"] for s in BEYOND)
+    for parts in ("fwd_parts", "bwd_parts"):
+        for tiles in (1, 2, 3, 4):  # (row tiles) with the reduction whole and split
+            assert {p[parts] > 1 for p in plans if p["tiles_m"] == tiles and p["r"]} == {False, True}, (parts, tiles)
+        assert any(p[parts] > 1 and p["r"] > 32 for p in plans) and any(p[parts] == 1 and p["r"] > 32 for p in plans)
+
+
+@pytest.mark.parametrize("shape", SHAPES + BEYOND, ids=["x".join(map(str, s)) for s in SHAPES + BEYOND])
 def test_narrow_parity(orc, shape):
     T, K, N, r = shape
+    assert lm.lora_few_token_plan(*shape)["taken"] == (shape in SHAPES)
     _announce(f"narrow T={T} K={K} N={N} r={r}")
     inp = lora_inputs(T, K, N, r, seed=sum(shape))
     s = 2.0
@@ -51,12 +69,13 @@ def test_narrow_parity(orc, shape):
     compare(got, ref, BF16, label=f"narrow {shape}")
 
 
-@pytest.mark.parametrize("T", [20, 60, 110])
-def test_narrow_zero_B_is_rank_0(T):
+@pytest.mark.parametrize("T,ranks", [(20, (4, 32, 36, 64)), (60, (4, 32)), (110, (4, 32))])
+def test_narrow_zero_B_is_rank_0(T, ranks):
     """With B = 0 the output is the rank-0 forward's bitwise, at every rank."""
-    K, N = 2056, 520
+    K, N = 2056, 2056
     _announce(f"narrow B=0 T={T}")
-    for r in (4, 32, 64):
+    for r in ranks:
+        assert lm.lora_few_token_plan(T, K, N, r)["taken"] and lm.lora_few_token_plan(T, K, N, 0)["taken"]
         inp = lora_inputs(T, K, N, r, seed=T)
         inp["B"].zero_()
         d = {k: v.cuda() for k, v in inp.items()}
@@ -64,8 +83,7 @@ def test_narrow_zero_B_is_rank_0(T):
         lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], y, None, 2.0)
         lm.lora_linear_fwd(d["x"], d["W"], None, None, y0)
         torch.cuda.synchronize()
-        if r <= 32:  # (ranks above 32 have tiles of their own)
-            assert torch.equal(y, y0)
+        assert torch.equal(y, y0), r
 
 
 @pytest.mark.parametrize("fill", [0x00, 0xFF, "random"])
@@ -74,14 +92,15 @@ def test_narrow_workspace_contents_and_reuse(orc, fill):
     serves calls of other sizes in between, and less of it the tiled kernels."""
     s = 2.0
     n = max(lm.lora_linear_workspace_bytes(op, T, K, N, r, lm.LORA_BF16)
-            for T, K, N, r in ((24, 3072, 3072, 16), (120, 2048, 1032, 8)) for op in (lm.LORA_OP_FWD, lm.LORA_OP_BWD))
+            for T, K, N, r in ((24, 3072, 3072, 16), (120, 2048, 2056, 8)) for op in (lm.LORA_OP_FWD, lm.LORA_OP_BWD))
     ws = torch.empty(n, dtype=torch.uint8, device="cuda")
     if fill == "random":
         ws.copy_(torch.randint(0, 256, ws.shape, dtype=torch.uint8, device="cuda"))
     else:
         ws.fill_(fill)
-    for it, (T, K, N, r) in enumerate([(24, 3072, 3072, 16), (120, 2048, 1032, 8), (24, 3072, 3072, 16)]):
+    for it, (T, K, N, r) in enumerate([(24, 3072, 3072, 16), (120, 2048, 2056, 8), (24, 3072, 3072, 16)]):
         _announce(f"narrow workspace fill={fill} T={T}")
+        assert lm.lora_few_token_plan(T, K, N, r)["taken"]
         inp = lora_inputs(T, K, N, r, seed=50 + it)
         d = {k: v.cuda() for k, v in inp.items()}
         o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
@@ -93,29 +112,36 @@ def test_narrow_workspace_contents_and_reuse(orc, fill):
         compare({k: v.cpu() for k, v in o.items()}, oracle_lora(orc, inp, s), BF16, label=f"fill={fill} it={it}")
 
 
-def test_narrow_least_workspace(orc):
-    """A workspace of the tiled kernels' size (the general bound: at most 64
-    padded rank columns per row of x and W) still serves the call."""
-    T, K, N, r = 24, 3072, 3072, 16
+@pytest.mark.parametrize("shape", [(24, 3072, 3072, 16), (48, 2056, 1032, 8), (63, 4096, 256, 4), (20, 2056, 520, 64),
+                                   (96, 4104, 1032, 16)], ids=lambda s: "x".join(map(str, s)))
+def test_tiled_kernels_at_few_tokens(orc, shape):
+    """A workspace of the tiled kernels' size still serves a call, through them."""
+    T, K, N, r = shape
     s = 2.0
+    p = lm.lora_few_token_plan(T, K, N, r)
+    assert p["fwd_tiled_bytes"] < p["fwd_bytes"] and p["bwd_tiled_bytes"] < p["bwd_bytes"]
+    _announce(f"tiled kernels T={T} K={K} N={N} r={r}")
     inp = lora_inputs(T, K, N, r, seed=5)
     d = {k: v.cuda() for k, v in inp.items()}
-    tiled = 4 * T * r * 4 + (T + N) * 64 * 2 + 768
-    assert tiled < lm.lora_linear_workspace_bytes(lm.LORA_OP_FWD, T, K, N, r, lm.LORA_BF16)
-    _announce("narrow shape with the tiled workspace")
-    y = torch.empty(T, N, dtype=BF16, device="cuda")
-    u = torch.empty(T, r, device="cuda")
-    ws = torch.empty(tiled, dtype=torch.uint8, device="cuda")
-    lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], y, u, s, ws=ws)
-    torch.cuda.synchronize()
     ref = oracle_lora(orc, inp, s)
-    compare({"y": y.cpu(), "u": u.cpu()}, {"y": ref["y"], "u": ref["u"]}, BF16, label="tiled workspace")
+    ws = torch.zeros(max(p["fwd_bytes"], p["bwd_bytes"]), dtype=torch.uint8, device="cuda")
+    for saved in (True, False):
+        o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
+             "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
+             "dB": torch.empty(N, r, device="cuda")}
+        lm.lora_linear_fwd(d["x"], d["W"], d["A"], d["B"], o["y"], o["u"], s, ws=ws[: p["fwd_tiled_bytes"]])
+        lm.lora_linear_bwd(d["x"], d["W"], d["A"], d["B"], o["u"] if saved else None, d["dy"], o["dx"], o["dA"], o["dB"],
+                           s, ws=ws[: p["bwd_tiled_bytes"]])
+        torch.cuda.synchronize()
+        assert int(ws[max(p["fwd_tiled_bytes"], p["bwd_tiled_bytes"]):].count_nonzero()) == 0
+        compare({k: v.cpu() for k, v in o.items()}, ref, BF16, label=f"tiled workspace saved={saved}")
 
 
 def test_narrow_graph_replay(orc):
     """Replays carry one tag: each must find the meetings' words as if new."""
-    T, K, N, r = 123, 1544, 1032, 16
+    T, K, N, r = 123, 2048, 2056, 16
     s = 2.0
+    assert lm.lora_few_token_plan(T, K, N, r)["taken"]
     d = {k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=60).items()}
     o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
          "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
