@@ -197,8 +197,6 @@ bool host_copy_mapped(const void *host, size_t bytes);  // whether [host, host +
 // GEMM launch; `side` (may be NULL) adds the token-reduction workgroups.
 hipError_t launch_gemm(const GemmArgs &g, Dtype dt, bool b_kmajor, const SideArgs *side,
                        hipStream_t st);
-// bf16 GEMM whose B is the quantized frozen weight (bits = 4 or 8), dequantized
-// into LDS; the LoRA step (r <= 64) runs first.
 // Ranges of k that launch_gemm_split sums apart for a plain k-major product
 // (1: it does not pay), and the product itself (bits 16: bf16 B, else
 // quantized): C bf16 = sum over the ranges, in ascending order, of their fp32
@@ -209,6 +207,8 @@ hipError_t launch_gemm_split_q(const GemmArgs &g, int bits, int splits, hipStrea
 
 // Whether launch_gemm_q runs the dequantizing direct-to-LDS tiles for g.
 bool gemm_q_direct(const GemmArgs &g, int bits, bool b_kmajor, bool with_side);
+// bf16 GEMM whose B is the quantized frozen weight (bits = 4 or 8), dequantized
+// into LDS; the LoRA step (r <= 64) runs first.
 hipError_t launch_gemm_q(const GemmArgs &g, int bits, bool b_kmajor, const SideArgs *side,
                          hipStream_t st);
 

@@ -83,7 +83,7 @@ constexpr int NW_BM = 32, NW_BN = 64;
 template <int RB, int NBUF, bool KMAJ>
 __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   constexpr int BM = NW_BM, BN = NW_BN, NWV = 4, NT = 64 * NWV;
-  constexpr int FM = BM / 32, FN = BN / 32;
+  constexpr int FN = BN / 32;  // blocks of 32 columns; one of 32 rows
   constexpr int A_B = BM * 128, B_B = BN * 128, U_B = RB * 32 * 128, STAGE = A_B + B_B + U_B;
   constexpr int A_PW = A_B / 1024 / NWV, B_PW = B_B / 1024 / NWV;  // loads per wave per stage
   constexpr int U_PC = U_B / 1024;                                 // 1 KB pieces of the rank columns
@@ -91,8 +91,8 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   static_assert(A_PW * 1024 * NWV == A_B && B_PW * 1024 * NWV == B_B && (U_PC % NWV == 0 || U_PC < NWV), "whole loads");
   constexpr int C = BN + RB * 32;  // columns of the summed tile
   constexpr int LDF = C + 4;       // its padded LDS row (floats)
-  constexpr int PLANE = 32 * LDF;  // one wave slice's share of 32 rows
-  constexpr int FIN = (BM * LDF + 3 * PLANE) * 4;
+  constexpr int PLANE = BM * LDF;  // one wave's share of it
+  constexpr int FIN = NWV * PLANE * 4;
   constexpr int LDS = NBUF * STAGE > FIN ? NBUF * STAGE : FIN;
   constexpr uint32_t OOB = 0x80000000u;
   __shared__ __align__(16) char smem[LDS];
@@ -185,8 +185,8 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
     } else {
       // k-rows of 2 BN bytes, swizzled so that the transposed reads of four
       // k-rows fall into distinct banks
-      const int row = BN == 128 ? 4 * q + (lane >> 4) : 8 * q + (lane >> 3);
-      const int c = BN == 128 ? (lane & 15) ^ (4 * (row & 3)) : (lane & 7) ^ (4 * ((row >> 1) & 1));
+      const int row = 8 * q + (lane >> 3);
+      const int c = (lane & 7) ^ (4 * ((row >> 1) & 1));
       kW[i] = row;
       oW[i] = c * 8 < ncols ? (uint32_t)(row * (int64_t)a.N * 2 + c * 16) : OOB;
     }
@@ -227,15 +227,11 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   };
 
   // ---- main loop -----------------------------------------------------------------
-  f32x16 acc[FM][FN], accu[FM][RB > 0 ? RB : 1];
+  f32x16 acc[FN], accu[RB > 0 ? RB : 1];
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+  for (int j = 0; j < FN; ++j) acc[j] = f32x16{};
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < RB; ++j) accu[i][j] = f32x16{};
+  for (int j = 0; j < RB; ++j) accu[j] = f32x16{};
   const int ca = ((2 * wk + half) ^ (lrow & 7) ^ ((lrow >> 3) & 1)) * 16;  // the lane's chunk of its rows
   const int iq = lane & 15, gq = lane >> 4;
   const int tr_k = 16 * wk + 8 * (gq >> 1) + (iq >> 2), tr_n = 16 * (gq & 1) + 4 * (iq & 3);
@@ -246,12 +242,11 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
                  __builtin_bit_cast(uint2, hi).y};
   };
   struct Frags {
-    u32x4 a[FM], b[FN], u[RB > 0 ? RB : 1];
+    u32x4 a, b[FN], u[RB > 0 ? RB : 1];
   };
   auto read_frags = [&](int st, Frags &f) __attribute__((always_inline)) {
     const char *sA = smem + (st % NBUF) * STAGE, *sB = sA + A_B, *sU = sB + B_B;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) f.a[i] = ld16(sA + (i * 32 + lrow) * 128 + ca);
+    f.a = ld16(sA + lrow * 128 + ca);
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int n = j * 32;
@@ -259,7 +254,7 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
         f.b[j] = ld16(sB + (n + lrow) * 128 + ca);
       } else {
         const int c = (n + tr_n) >> 3;
-        const int sw = BN == 128 ? c ^ (4 * (tr_k & 3)) : c ^ (4 * ((tr_k >> 1) & 1));
+        const int sw = c ^ (4 * ((tr_k >> 1) & 1));
         f.b[j] = tr_read(sB + tr_k * (2 * BN) + sw * 16 + (tr_n & 7) * 2, 2 * BN);
       }
     }
@@ -289,13 +284,9 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
     issue(st + NBUF);
     read_frags(st + 1, next);
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int j = 0; j < FN; ++j) mma32(BF16(), acc[j], f.b[j], f.a);
 #pragma unroll
-      for (int j = 0; j < FN; ++j) mma32(BF16(), acc[i][j], f.b[j], f.a[i]);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < RB; ++j) mma32(BF16(), accu[i][j], f.u[j], f.a[i]);
+    for (int j = 0; j < RB; ++j) mma32(BF16(), accu[j], f.u[j], f.a);
   };
   {
 #pragma unroll
@@ -318,15 +309,15 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   // values of its dA block, as matrix-core fragments: loaded ahead of the
   // sums, which hide their latency.
   const uint16_t *P = (const uint16_t *)a.P;
-  constexpr int NS = RB * 2, NBLK = FM * (BN / 32), OB = (NBLK + NWV - 1) / NWV;  // rank slices; output blocks per wave
-  constexpr int DB = RB * (BN / 32);                                             // dA blocks, at most one per wave
-  static_assert(DB <= NWV, "one dA block per wave");
+  constexpr int NS = RB * 2;           // rank slices
+  constexpr int DB = RB * (BN / 32);   // dA blocks
+  static_assert(FN <= NWV && DB <= NWV, "at most one output block and one dA block per wave");
   const int ns = (r + 15) / 16;
   struct EndP {
     uint32_t w[NS > 0 ? NS : 1][4];
   };
-  auto load_p = [&](int b, EndP &e) __attribute__((always_inline)) {
-    const int n = n0 + (b / FM) * 32 + lrow;  // the lane's column of the operand
+  auto load_p = [&](EndP &e) __attribute__((always_inline)) {
+    const int n = n0 + wv * 32 + lrow;  // the lane's column of the operand
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int j0 = 16 * s + 8 * half;
@@ -364,45 +355,39 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
         e.w[s][h] = lo | (hi << 16);
       }
   };
-  EndP ep[OB];
+  EndP ep;
   EndX ex;
   if constexpr (RB > 0) {
-    if (a.out) {
-#pragma unroll
-      for (int o = 0; o < OB; ++o)
-        if (wv + o * NWV < NBLK) load_p(wv + o * NWV, ep[o]);
-    }
+    if (a.out && wv < FN) load_p(ep);
     if constexpr (KMAJ) if (wv < DB) load_x(ex);
   }
 
-  // ---- sum of the four k-slices, 32 rows at a time --------------------------------
-  // Rows [32 i, 32 i + 32) of the tile F; slice 0's share is written in place,
-  // the others' behind F.  A lane holds row lane % 32 and runs of 4 columns.
-  float *F = (float *)smem, *PL = F + BM * LDF;
+  // ---- sum of the four k-slices -----------------------------------------------------
+  // Slice 0's share is written in place (the tile F), the others' behind F.  A
+  // lane holds row lane % 32 and runs of 4 columns.
+  float *F = (float *)smem, *PL = F + PLANE;
   const int64_t tile_id = (int64_t)nt * a.tiles_m + mt;
   const __amdgpu_buffer_rsrc_t rsS = nw_rsrc(a.slots ? a.slots + tile_id * a.parts * (BM * C) : nullptr,
                                              a.parts > 1 ? (int64_t)a.parts * BM * C * 4 : 0);
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    float *dst = wk == 0 ? F + i * PLANE : PL + (wk - 1) * PLANE;
+  {
+    float *dst = F + wk * PLANE;
     auto put = [&](const f32x16 &v, int col) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         *(f32x4 *)(dst + lrow * LDF + col + 8 * q + 4 * half) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     };
 #pragma unroll
-    for (int j = 0; j < FN; ++j) put(acc[i][j], j * 32);
+    for (int j = 0; j < FN; ++j) put(acc[j], j * 32);
 #pragma unroll
-    for (int j = 0; j < RB; ++j) put(accu[i][j], BN + j * 32);
+    for (int j = 0; j < RB; ++j) put(accu[j], BN + j * 32);
     __syncthreads();
-    for (int e = tid; e < 32 * C / 4; e += NT) {
+    for (int e = tid; e < BM * C / 4; e += NT) {
       const int row = e / (C / 4), col = e % (C / 4) * 4;
-      float *f = F + i * PLANE + row * LDF + col;
-      const float *p = PL + row * LDF + col;
+      float *f = F + row * LDF + col;
       f32x4 v = *(f32x4 *)f;
 #pragma unroll
-      for (int w = 0; w < 3; ++w) v += *(const f32x4 *)(p + w * PLANE);
-      if (a.parts > 1) nw_store(rsS, ((part * BM + i * 32 + row) * C + col) * 4, v);
+      for (int w = 1; w < NWV; ++w) v += *(const f32x4 *)(f + w * PLANE);
+      if (a.parts > 1) nw_store(rsS, ((part * BM + row) * C + col) * 4, v);
       else *(f32x4 *)f = v;
     }
     __syncthreads();
@@ -470,31 +455,24 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
     }
     return pack_vec(BF16(), f);
   };
-  if (a.out) {
+  if (a.out && wv < FN) {
+    f32x16 c;
 #pragma unroll
-    for (int o = 0; o < OB; ++o) {
-      const int b = wv + o * NWV;
-      if (b >= NBLK) break;
-      const int i = b % FM, j = b / FM;
-      f32x16 c;
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = *(const f32x4 *)(F + lrow * LDF + wv * 32 + 8 * q + 4 * half);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = *(const f32x4 *)(F + (i * 32 + lrow) * LDF + j * 32 + 8 * q + 4 * half);
+      for (int e = 0; e < 4; ++e) c[4 * q + e] = v[e];
+    }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) c[4 * q + e] = v[e];
-      }
+    for (int s = 0; s < NS; ++s)
+      if (s < ns) mma32(BF16(), c, u32x4{ep.w[s][0], ep.w[s][1], ep.w[s][2], ep.w[s][3]}, su(lrow, s));
+    const int m = m0 + lrow;
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        if (s < ns)
-          mma32(BF16(), c, u32x4{ep[o].w[s][0], ep[o].w[s][1], ep[o].w[s][2], ep[o].w[s][3]}, su(i * 32 + lrow, s));
-      const int m = m0 + i * 32 + lrow;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + j * 32 + 8 * q + 4 * half;
-        if (m < a.T && col < a.N)
-          *(uint2 *)((uint16_t *)a.out + (int64_t)m * a.N + col) =
-              make_uint2(pack_bf16x2(c[4 * q], c[4 * q + 1]), pack_bf16x2(c[4 * q + 2], c[4 * q + 3]));
-      }
+    for (int q = 0; q < 4; ++q) {
+      const int col = n0 + wv * 32 + 8 * q + 4 * half;
+      if (m < a.T && col < a.N)
+        *(uint2 *)((uint16_t *)a.out + (int64_t)m * a.N + col) =
+            make_uint2(pack_bf16x2(c[4 * q], c[4 * q + 1]), pack_bf16x2(c[4 * q + 2], c[4 * q + 3]));
     }
   }
 
