@@ -53,7 +53,9 @@
  *
  * Determinism: every reduction (over tokens, over the split feature axis of
  * the rank-r products, across waves) adds its parts in a fixed order, so
- * identical inputs give bitwise identical outputs.  Atomics appear only where
+ * identical inputs give bitwise identical outputs, given workspaces that
+ * select the same kernels (see lora_linear_workspace_bytes and
+ * frozen_linear_split_bytes).  Atomics appear only where
  * they cannot change a result: the counters of the fused hand-over (they
  * order work; see lora_handover_giveups); the part counts of the dA / dB
  * token reductions that run as token parts (they pick the part that adds
@@ -146,8 +148,9 @@ lora_status_t frozen_linear_bwd_dx(const void *dy, const void *W, void *dx, int6
                                    size_t ws_bytes, void *hip_stream);
 /* Workspace with which frozen_linear_bwd_dx (and its quantized form) splits a
  * long reduction over CUs that the output's tiles would leave idle; 0 where
- * that does not pay, (size_t)-1 for rejected sizes.  Optional: with less, or
- * none, the call runs unsplit. */
+ * that does not pay, (size_t)-1 for rejected sizes; at most 64 MiB.  Optional:
+ * with less, or none, the call runs unsplit, which sums in another order (the
+ * results then differ by the rounding of fp32 sums). */
 size_t frozen_linear_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt);
 
 /* ---- Quantized frozen base ------------------------------------------------

@@ -182,7 +182,8 @@ def _ws(ws, nbytes: int, like, stream=None):
 
 def _ws_optional(nbytes: int, like, stream=None):
     """A temporary workspace that speeds a call up but is not needed by it:
-    None where the device has no room."""
+    None where the device has no room.  (A caller that wants neither the
+    allocation nor its failure passes a workspace of its own.)"""
     import torch
 
     try:
@@ -245,7 +246,12 @@ def _split_ws(T, d_in, d_out, dt, like, stream):
 
 
 def frozen_linear_bwd_dx(dy, W, dx, ws=None, stream=None):
-    """Rank-0 frozen linear input gradient dx = dy W."""
+    """Rank-0 frozen linear input gradient dx = dy W.
+
+    Without `ws`, a long reduction is split over a temporary workspace of up to 64
+    MiB (frozen_linear_split_bytes), or, where the device has no room for it, runs
+    unsplit, with sums in another order.  A `ws` of the caller's fixes which: one of
+    that size splits, a smaller one (an empty tensor too) does not."""
     T, d_out = dy.shape
     d_in = W.shape[1]
     dt = _dtype_code(dy)
@@ -359,7 +365,12 @@ def lm_head_reduced_ce(h, W, rows, J, tpos, loss_rows, loss_total=None, dh=None,
 # --- top-k similarity table ---------------------------------------------------------
 def topk_table_build(W, k: int, table=None, values=None, ws=None, stream=None):
     """table [V, k] int32 (and optionally values [V, k] fp32) of each token's k
-    most cosine-similar tokens."""
+    most cosine-similar tokens.
+
+    Without `ws`, a temporary workspace of topk_table_workspace_bytes_paired (7.4 GB
+    at V = 128256, k = 1000) is taken where the device has room, else the smaller
+    one of topk_table_workspace_bytes; a `ws` of the caller's fixes which.  Table and
+    values are the same bitwise."""
     import torch
 
     V, D = W.shape

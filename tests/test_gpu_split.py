@@ -76,3 +76,41 @@ def test_frozen_split_sizes():
     assert _split_bytes(1500, 2048, 2056) == 0        # the planes would cost more than the split gains
     assert lm.lib().frozen_linear_split_bytes(64, 256, 8192, lm.LORA_F32) == 0
     assert lm.lib().frozen_linear_split_bytes(64, 100, 8192, lm.LORA_BF16) == 2 ** 64 - 1
+
+
+def test_no_room_for_the_optional_workspaces():
+    """Where the allocator has no room, the split dx runs unsplit and the similarity
+    table over row batches; a caller's workspace fixes the choice."""
+    _announce("no room for the optional workspaces")
+    T, d_in, d_out = 1024, 3072, 20008
+    g = torch.Generator().manual_seed(5)
+    dy = torch.randn(T, d_out, generator=g).bfloat16().cuda()
+    W = (torch.randn(d_out, d_in, generator=g) * 0.02).bfloat16().cuda()
+    E = torch.randn(16400, 64, generator=g).bfloat16().cuda()
+    n = _split_bytes(T, d_in, d_out)
+    split, unsplit, full = (torch.empty(T, d_in, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    tables = [torch.empty(16400, 100, dtype=torch.int32, device="cuda") for _ in range(2)]
+    batched = lm.lib().topk_table_workspace_bytes(16400, 64, 100)
+    small = torch.empty(batched, dtype=torch.uint8, device="cuda")
+    lm.frozen_linear_bwd_dx(dy, W, split, ws=torch.empty(n, dtype=torch.uint8, device="cuda"))
+    lm.frozen_linear_bwd_dx(dy, W, unsplit, ws=dy.new_empty(0))
+    lm.topk_table_build(E, 100, tables[0])
+    torch.cuda.synchronize()
+    del small
+    torch.cuda.empty_cache()
+    free = torch.empty(batched, dtype=torch.uint8, device="cuda")  # (room for the smaller one, given back below)
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+        lm.frozen_linear_bwd_dx(dy, W, full)
+        del free
+        lm.topk_table_build(E, 100, tables[1])
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(full, unsplit)
+    _check(split, dy, W)
+    _check(unsplit, dy, W)
+    assert torch.equal(tables[0], tables[1])
