@@ -314,11 +314,11 @@ lora_status_t lora_ckpt_backward(const lora_node_t *nodes, int n, int64_t T, con
  * du = s dy B are computed; and over how many consecutive token ranges each
  * output block of the token reductions dA = du^T x and dB = s dy^T u runs
  * in the unfused dx launch (bwd_side_parts; 1 = all T in one workgroup).
- * This is the tiled kernels' configuration.  Calls of up to 64 tokens (up to
+ * This is the tiled kernels' configuration.  Most calls of up to 64 tokens (up to
  * 128 where d_in x d_out >= 2^22), bf16, r a multiple of 4 up to 64 (32 above
  * 32 tokens), given the workspace that lora_linear_workspace_bytes reports,
- * run the few-token kernel instead: tiles of 32 x 64 with the rank-r pass in
- * them, the reduction in up to four parts.
+ * run the few-token kernel instead (lora_few_token_plan): tiles of 32 x 64 with
+ * the rank-r pass in them, the reduction in up to four parts.
  * Errors as for the entry points' size checks. */
 typedef struct {
   int fwd_tile_m, fwd_tile_n, fwd_fused, fwd_u_parts;
@@ -328,14 +328,15 @@ typedef struct {
 lora_status_t lora_linear_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, lora_dtype_t dt,
                                lora_plan_t *plan);
 
-/* Whether calls of these sizes run the few-token kernel (`taken`) once they are
- * given a workspace of fwd_bytes (bwd_bytes), its tiles of 32 tokens by 64
- * columns of y (dx) and the parts of the reduction; and the workspace of the
- * tiled kernels, which serves the call as well.  Host logic only; errors as for
- * lora_linear_plan. */
+/* Whether the forward and the backward of these sizes run the few-token kernel
+ * once they are given a workspace of fwd_bytes (bwd_bytes), its tiles of 32
+ * tokens by 64 columns of y (dx) and the parts of the reduction (0 where it is not
+ * taken; bwd_bytes may then still count a u recomputed as that kernel's forward
+ * sums it); and the workspace of the tiled kernels, which serves the call as
+ * well.  Host logic only; errors as for lora_linear_plan. */
 typedef struct {
-  int taken, tiles_m;
-  int fwd_tiles_n, fwd_parts, bwd_tiles_n, bwd_parts;
+  int fwd_taken, fwd_tiles_m, fwd_tiles_n, fwd_parts;
+  int bwd_taken, bwd_tiles_m, bwd_tiles_n, bwd_parts;
   size_t fwd_bytes, bwd_bytes, fwd_tiled_bytes, bwd_tiled_bytes;
 } lora_few_token_plan_t;
 lora_status_t lora_few_token_plan(int64_t T, int64_t d_in, int64_t d_out, int64_t r, lora_dtype_t dt,

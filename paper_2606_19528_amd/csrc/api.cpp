@@ -243,35 +243,78 @@ BwdLayout bwd_layout(int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt
   return L;
 }
 
-// Few tokens: the workspace of the narrow kernels, beside that of the tiled
-// ones.  A call reports the larger of the two, runs the narrow kernel when it
-// is given that much and the tiled kernels when it is given only theirs.
+// Which directions of a call of few tokens run the few-token kernel.  Up to 256
+// tiles, one a CU, it wins at every size measured (1200 of up to 128 tokens and
+// 16384 columns: 0.02 to 0.97 of the tiled kernels' time), but for a rank-0 dx over
+// more than 9216 columns that are not whole 128-byte lines (each line is then read
+// by two workgroups of different XCDs: 1.1 - 1.7, at 8368 columns still 0.8 - 1.0).
+// With more tiles a CU's load path is taken a second time, and the few-token kernel
+// stays only where the tiled kernels are far from their best:
+//   forward, fused: up to 64 tokens over up to 512 columns of x, where the
+//     hand-over is most of the time (0.7 - 0.93); else it loses (1.0 - 2.0: 96
+//     tokens of 2048 -> 11008 at r = 16 21.2 against 16.0 us), as at rank 0;
+//   forward, unfused: ranks that are not multiples of 8, which the tiled kernels
+//     pad (0.05 - 1.0), up to 96 tokens or a tile count times d_in of 5 M (beyond 0.9 - 1.4);
+//     other ranks (wide outputs) up to half of that and 64 tokens, or 96 over 1024
+//     columns of x (0.6 - 0.9, beyond 1.0 - 1.6);
+//   backward, fused, where few producers run the dA / dB items: always (0.1 - 0.9);
+//   backward, unfused: ranks that are not multiples of 8 up to 64 tokens or 320
+//     tiles (0.6 - 1.04), and at r >= 20 over 2048 rows of W (0.6 - 1.1); else it
+//     loses (1.0 - 1.8: 128 tokens of 8192 -> 3072 at r = 4 42.5 against 27.6 us),
+//     as at rank 0 (1.0 - 1.7).
+struct FewRule {
+  bool fwd, bwd;
+};
+FewRule few_rule(int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt) {
+  const NarrowPlan f = narrow_plan(T, N, K, r), b = narrow_plan(T, K, N, r);
+  if (dt != LORA_BF16 || !f.ok || !b.ok) return FewRule{};
+  const int64_t ft = (int64_t)f.tiles_m * f.tiles_n, bt = (int64_t)b.tiles_m * b.tiles_n;
+  FewRule e{ft <= 256, bt <= 256 && (r > 0 || K % 64 == 0 || K < 9216)};
+  if (!e.fwd && r > 0) {
+    if (fuse_ok(T, N, K, r, dt)) e.fwd = T <= 64 && K <= 512;
+    else if (r % 8 != 0) e.fwd = T <= 96 || ft * K <= (5 << 20);
+    else e.fwd = (T <= 64 || (T <= 96 && K >= 1024)) && ft * K <= (5 << 19);
+  }
+  if (!e.bwd && r > 0)
+    e.bwd = fuse_ok(T, K, N, r, dt, true) || (r % 8 != 0 && (T <= 64 || bt <= 320 || (r >= 20 && N >= 2048)));
+  return e;
+}
+
+// The workspace of the few-token kernel, beside that of the tiled ones: a call
+// reports the larger of the two and runs the tiled kernels when it is given only
+// theirs.  A backward that recomputes u sums it as the forward did: where only
+// the forward runs the few-token kernel, behind the tiled kernels' workspace
+// (`taken` false, `u_narrow` true); where only the backward does, in the tiled
+// forward's partial sums.
 struct NarrowWs {
-  NarrowPlan p;
+  NarrowPlan p, pu;
+  bool taken, u_narrow;
   size_t sync, slots, da, u, total;
 };
 NarrowWs narrow_ws(bool bwd, int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt) {
   NarrowWs L{};
-  if (dt != LORA_BF16) return L;
-  L.p = bwd ? narrow_plan(T, K, N, r) : narrow_plan(T, N, K, r);
-  if (!L.p.ok) return L;
-  NarrowPlan pu{};
-  if (bwd && r > 0) {  // u recomputed, in the forward's order of summation
-    pu = narrow_plan(T, N, K, r);
-    if (!pu.ok) return NarrowWs{};
-    pu.slot_bytes /= pu.tiles_n;
-    pu.flags = pu.tiles_m * pu.parts;
-  }
+  const FewRule few = few_rule(T, K, N, r, dt);
+  L.taken = bwd ? few.bwd : few.fwd;
+  L.u_narrow = bwd && r > 0 && few.fwd;
+  if (!L.taken && !L.u_narrow) return L;
   size_t off = 0;
+  if (L.taken) L.p = bwd ? narrow_plan(T, K, N, r) : narrow_plan(T, N, K, r);
+  else off = round256(bwd_layout(T, K, N, r, dt).total);
+  if (L.u_narrow) {
+    L.pu = narrow_plan(T, N, K, r);
+    L.pu.slot_bytes /= L.pu.tiles_n;
+    L.pu.tiles_n = 1;
+    L.pu.flags = L.pu.tiles_m * L.pu.parts;
+  }
   L.sync = off;
-  const bool meets = L.p.parts > 1 || pu.parts > 1 || (bwd && r > 0 && L.p.tiles_m > 1);
-  off += meets ? round256((size_t)std::max(L.p.flags, pu.flags) * sizeof(meet_word)) : 0;
+  const bool meets = L.p.parts > 1 || L.pu.parts > 1 || (L.taken && bwd && r > 0 && L.p.tiles_m > 1);
+  off += meets ? round256((size_t)std::max(L.p.flags, L.pu.flags) * sizeof(meet_word)) : 0;
   L.slots = off;
-  off += round256(std::max(L.p.slot_bytes, pu.slot_bytes));
+  off += round256(std::max(L.p.slot_bytes, L.pu.slot_bytes));
   L.da = off;
   off += bwd ? round256(L.p.da_bytes) : 0;
   L.u = off;
-  off += bwd ? round256((size_t)T * r * 4) : 0;
+  if (bwd && r > 0) off += round256((size_t)(L.u_narrow ? 1 : bwd_layout(T, K, N, r, dt).sp_u.nsplit) * T * r * 4);
   L.total = off;
   return L;
 }
@@ -419,7 +462,7 @@ hipError_t run_gemm(const GemmArgs &g, Dtype d, const QWeight *q, bool kmajor, c
 // Whether the caller's workspace serves the narrow kernel: large enough,
 // aligned and clear of the operands (else the tiled kernels take the call or refuse it).
 bool narrow_fits(const NarrowWs &nw, void *ws, size_t ws_bytes, const std::vector<Range> &operands) {
-  if (!nw.p.ok) return false;
+  if (!nw.taken && !nw.u_narrow) return false;
   if (nw.total == 0) return true;
   return ws && ws_bytes >= nw.total && aligned16(ws) && !any_overlap({rng(ws, (int64_t)nw.total)}, operands);
 }
@@ -576,13 +619,14 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
     if (p && !aligned16(p)) return fail(LORA_EINVAL, "pointers must be 16-byte aligned");
   const size_t es = esize(dt);
   const NarrowWs nw = qc ? NarrowWs{} : narrow_ws(true, T, d_in, d_out, r, dt);
-  const bool narrow =
+  const bool few =
       narrow_fits(nw, ws, ws_bytes, {rng(x, T * d_in * es), rng(W, d_out * d_in * es), rng(dy, T * d_out * es),
                                      rng(dx, T * d_in * es), rng(A, r * d_in * es), rng(B, d_out * r * es),
                                      rng(u_saved, T * r * 4), rng(dA, r * d_in * 4), rng(dB, d_out * r * 4)});
+  const bool narrow = few && nw.taken, narrow_u = few && nw.u_narrow && !u_saved;
   const size_t least = bwd_layout(T, d_in, d_out, r, dt).total;
   if ((s = check_ws(ws, ws_bytes, least)) != LORA_OK) return s;
-  const size_t need = std::max(least, narrow ? nw.total : 0);
+  const size_t need = std::max(least, narrow || narrow_u ? nw.total : 0);
   std::vector<Range> ins = {rng(dy, T * d_out * es)};
   if (qc) ins.insert(ins.end(), qins.begin(), qins.end());
   else ins.push_back(rng(W, d_out * d_in * es));
@@ -608,31 +652,51 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   g.M = dx ? (int)T : 0; g.N = (int)d_in; g.K = (int)d_out;
   g.C = dx; g.ldc = d_in;
   set_qweight(g, qc ? &qw : nullptr);
+  // u = x A^T rematerialised instead of stored, as the forward summed it: by the
+  // few-token kernel, or in the tiled forward's partial sums at `out`.
+  auto recompute_u = [&](float *out, int *parts) -> hipError_t {
+    Timed t(K_LORA_DOWN, st);
+    hipError_t ue;
+    if (narrow_u) {
+      NarrowArgs a{};
+      a.X = x; a.W = W; a.V = A; a.P = B;
+      a.T = (int)T; a.N = 0; a.K = (int)d_in; a.r = (int)r; a.scale = scale;
+      a.sync = (meet_word *)((char *)ws + nw.sync);
+      a.slots = (float *)((char *)ws + nw.slots);
+      a.u_out = out;
+      a.gen = next_tag();
+      *parts = 1;
+      ue = launch_narrow(a, nw.pu, false, st);
+    } else {
+      const RowSplit sp = bwd_layout(T, d_in, d_out, r, dt).sp_u;
+      RowArgs ra{};
+      ra.X = x; ra.ldx = d_in; ra.M = (int)T; ra.L = (int)d_in;
+      ra.V = A; ra.ldv = d_in; ra.vmode = V_ROW; ra.r = (int)r;
+      ra.nsplit = sp.nsplit; ra.seg = sp.seg; ra.mb = sp.mb;
+      ra.out_mult = 1.0f; ra.out = out; ra.out_stride = T * r;
+      *parts = sp.nsplit;
+      ue = launch_row_skinny(ra, d, st);
+    }
+    t.done();
+    return ue;
+  };
   if (narrow) {
     char *wsb = (char *)ws;
     NarrowArgs a{};
-    a.T = (int)T; a.r = (int)r; a.scale = scale;
+    a.X = dy; a.W = W; a.V = B; a.P = A; a.out = dx;
+    a.T = (int)T; a.N = (int)d_in; a.K = (int)d_out; a.r = (int)r; a.scale = scale;
     a.sync = (meet_word *)(wsb + nw.sync);
     a.slots = (float *)(wsb + nw.slots);
     a.da_slots = (float *)(wsb + nw.da);
-    const float *u = u_saved;
-    if (r > 0 && !u) {  // rematerialise u = x A^T as the forward summed it
-      NarrowPlan pu = narrow_plan(T, d_out, d_in, r);
-      pu.tiles_n = 1;
-      NarrowArgs b = a;
-      b.X = x; b.W = W; b.V = A; b.P = B;
-      b.N = 0; b.K = (int)d_in;
-      b.u_out = (float *)(wsb + nw.u);
-      b.gen = next_tag();
-      Timed t(K_LORA_DOWN, st);
-      e = launch_narrow(b, pu, false, st);
-      t.done();
+    a.xin = x; a.u_in = u_saved; a.dA = dA; a.dB = dB;
+    if (r > 0 && !u_saved) {
+      float *u = (float *)(wsb + nw.u);
+      int parts = 1;
+      e = recompute_u(u, &parts);
+      if (e == hipSuccess && parts > 1) e = launch_narrow_sum(u, parts, (int)(T * r), u, st);
       if (e != hipSuccess) return hip_fail(e, "lora_down launch");
-      u = b.u_out;
+      a.u_in = u;
     }
-    a.X = dy; a.W = W; a.V = B; a.P = A; a.out = dx;
-    a.N = (int)d_in; a.K = (int)d_out;
-    a.xin = x; a.u_in = u; a.dA = dA; a.dB = dB;
     a.gen = next_tag();
     Timed t(K_GEMM_BWD_DX, st);
     e = launch_narrow(a, nw.p, true, st);
@@ -650,18 +714,9 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   char *wsb = (char *)ws;
   const float *u = u_saved;
   int u_parts = 1;
-  if (!u) {  // rematerialise u = x A^T instead of having stored it
-    RowArgs ra{};
-    ra.X = x; ra.ldx = d_in; ra.M = (int)T; ra.L = (int)d_in;
-    ra.V = A; ra.ldv = d_in; ra.vmode = V_ROW; ra.r = (int)r;
-    ra.nsplit = L.sp_u.nsplit; ra.seg = L.sp_u.seg; ra.mb = L.sp_u.mb;
-    ra.out_mult = 1.0f; ra.out = (float *)(wsb + L.u); ra.out_stride = T * r;
-    Timed t(K_LORA_DOWN, st);
-    e = launch_row_skinny(ra, d, st);
-    t.done();
-    if (e != hipSuccess) return hip_fail(e, "lora_down launch");
-    u = (const float *)(wsb + L.u);
-    u_parts = L.sp_u.nsplit;
+  if (!u) {
+    u = (const float *)(wsb + (narrow_u ? nw.u : L.u));
+    if ((e = recompute_u((float *)u, &u_parts)) != hipSuccess) return hip_fail(e, "lora_down launch");
   }
   const int ns = L.sp_du.nsplit;
   float *du = (float *)(wsb + L.du);
@@ -1125,18 +1180,18 @@ lora_status_t lora_few_token_plan(int64_t T, int64_t d_in, int64_t d_out, int64_
   if (s != LORA_OK) return s;
   const NarrowWs f = narrow_ws(false, T, d_in, d_out, r, dt), b = narrow_ws(true, T, d_in, d_out, r, dt);
   lora_few_token_plan_t p{};
+  p.fwd_taken = f.taken;
+  p.fwd_tiles_m = f.p.tiles_m;
+  p.fwd_tiles_n = f.p.tiles_n;
+  p.fwd_parts = f.p.parts;
+  p.bwd_taken = b.taken;
+  p.bwd_tiles_m = b.p.tiles_m;
+  p.bwd_tiles_n = b.p.tiles_n;
+  p.bwd_parts = b.p.parts;
+  p.fwd_bytes = f.total;
+  p.bwd_bytes = b.total;
   p.fwd_tiled_bytes = fwd_layout(T, d_in, d_out, r, dt).total;
   p.bwd_tiled_bytes = bwd_layout(T, d_in, d_out, r, dt).total;
-  p.taken = f.p.ok && b.p.ok;
-  if (p.taken) {
-    p.tiles_m = f.p.tiles_m;
-    p.fwd_tiles_n = f.p.tiles_n;
-    p.fwd_parts = f.p.parts;
-    p.bwd_tiles_n = b.p.tiles_n;
-    p.bwd_parts = b.p.parts;
-    p.fwd_bytes = f.total;
-    p.bwd_bytes = b.total;
-  }
   *plan = p;
   return LORA_OK;
 }

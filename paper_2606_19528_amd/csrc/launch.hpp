@@ -359,6 +359,8 @@ NarrowPlan narrow_plan(int64_t T, int64_t N, int64_t K, int64_t r);
 // Workspace that lora_linear_bwd cannot do without (the tiled kernels').
 size_t bwd_least_workspace(int64_t T, int64_t d_in, int64_t d_out, int64_t r, bool bf16);
 hipError_t launch_narrow(NarrowArgs a, const NarrowPlan &p, bool k_major, hipStream_t st);
+// u[i] = sum of planes[p * n + i] over p < parts, ascending; u may be planes.
+hipError_t launch_narrow_sum(const float *planes, int parts, int n, float *u, hipStream_t st);
 
 // Split of a row-skinny product over its reduction axis L, and rows per
 // workgroup.  Short T (below 2048): one 16-row tile per workgroup, enough

@@ -523,17 +523,33 @@ __global__ __launch_bounds__(256) void narrow_kernel(NarrowArgs a) {
   }
 }
 
+// u = the sum of `parts` planes of n, in ascending order, as the tiled kernels add
+// them.  (A pass of its own: a loop over the planes in the dB workgroups above
+// kept their loads from being in flight at once, 23 -> 38 us for 48 tokens of
+// 11008 -> 2048.)
+__global__ __launch_bounds__(256) void narrow_sum_kernel(const float *planes, int parts, int n, float *u) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float v = planes[i];
+  for (int p = 1; p < parts; ++p) v += planes[(int64_t)p * n + i];
+  u[i] = v;
+}
+
+hipError_t launch_narrow_sum(const float *planes, int parts, int n, float *u, hipStream_t st) {
+  hipLaunchKernelGGL(narrow_sum_kernel, dim3((n + 255) / 256), dim3(256), 0, st, planes, parts, n, u);
+  return hipGetLastError();
+}
+
 // ---- the shape of a call -----------------------------------------------------------
 NarrowPlan narrow_plan(int64_t T, int64_t N, int64_t K, int64_t r) {
   NarrowPlan p{};
-  // Up to 64 tokens (32 above 32 rank columns) at every size; up to 128 where W
-  // has 2^22 weights or more, else the row tiles' meeting over dA costs more
-  // than the launch saves.  fwd + bwd in us against the tiled kernels: 24 tokens
-  // of 3072 -> 3072 26 against 160, 64 33 against 93, 128 34 against 59; 50 of
-  // 8192 -> 3072 49 against 174; 128 of 3072 -> 8192 62 against 99; but 128 of
-  // 256 -> 256 19 against 18, 128 of 2048 -> 256 with r = 64 43 against 34.  One
-  // rule for both directions, so that a recomputed u is summed as the forward
-  // summed it.  (A part's W rows lie within 31-bit offsets.)
+  // Up to 64 tokens (32 above 32 rank columns); up to 128 where W has 2^22
+  // weights or more, else the row tiles' meeting over dA costs more than the launch
+  // saves; few_rule (api.cpp) says which directions.  fwd + bwd in us against the
+  // tiled kernels: 24 tokens of 3072 -> 3072 25 against 160, 64 32 against 93, 128
+  // 33 against 59; 50 of 8192 -> 3072 48 against 175; but 128 of 256 -> 256 19
+  // against 18, 128 of 2048 -> 256 with r = 64 43 against 34.  (A part's W rows lie
+  // within 31-bit offsets.)
   if (T < 1 || T > NARROW_MAX_T || r < 0 || r > 64 || r % 4 || N * K >= (int64_t(1) << 30)) return p;
   if ((T > 64 && N * K < (int64_t(1) << 22)) || (T > 32 && r > 32)) return p;
   p.tiles_m = (int)((T + NW_BM - 1) / NW_BM);

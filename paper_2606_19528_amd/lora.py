@@ -36,8 +36,8 @@ class _Plan(ctypes.Structure):
 
 class _FewTokenPlan(ctypes.Structure):
     """lora_few_token_plan_t of the C ABI."""
-    _fields_ = [(n, ctypes.c_int) for n in ("taken", "tiles_m", "fwd_tiles_n", "fwd_parts", "bwd_tiles_n",
-                                            "bwd_parts")]
+    _fields_ = [(n, ctypes.c_int) for n in ("fwd_taken", "fwd_tiles_m", "fwd_tiles_n", "fwd_parts",
+                                            "bwd_taken", "bwd_tiles_m", "bwd_tiles_n", "bwd_parts")]
     _fields_ += [(n, ctypes.c_size_t) for n in ("fwd_bytes", "bwd_bytes", "fwd_tiled_bytes", "bwd_tiled_bytes")]
 
 
@@ -470,8 +470,8 @@ def lora_linear_plan(T: int, d_in: int, d_out: int, r: int, dt: int = LORA_BF16)
 
 
 def lora_few_token_plan(T: int, d_in: int, d_out: int, r: int, dt: int = LORA_BF16) -> dict:
-    """Whether the few-token kernel takes calls of these sizes, its tiles and parts,
-    and the workspaces that it and the tiled kernels want."""
+    """Whether the few-token kernel takes the forward and the backward of these sizes,
+    its tiles and parts, and the workspaces that it and the tiled kernels want."""
     p = _FewTokenPlan()
     _check(lib().lora_few_token_plan(T, d_in, d_out, r, dt, ctypes.byref(p)), "lora_few_token_plan")
     return {n: getattr(p, n) for n, _ in _FewTokenPlan._fields_}

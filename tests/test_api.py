@@ -381,14 +381,25 @@ def test_plan_query():
 
 def test_few_token_plan_query():
     p = lm.lora_few_token_plan(64, 2048, 2048, 16)
-    assert (p["taken"], p["tiles_m"], p["fwd_tiles_n"], p["fwd_parts"], p["bwd_parts"]) == (1, 2, 32, 2, 2)
+    assert (p["fwd_taken"], p["fwd_tiles_m"], p["fwd_tiles_n"], p["fwd_parts"]) == (1, 2, 32, 2)
+    assert (p["bwd_taken"], p["bwd_tiles_m"], p["bwd_tiles_n"], p["bwd_parts"]) == (1, 2, 32, 2)
     for op, name in ((lm.LORA_OP_FWD, "fwd"), (lm.LORA_OP_BWD, "bwd")):
         n = lm.lora_linear_workspace_bytes(op, 64, 2048, 2048, 16, lm.LORA_BF16)
         assert n == max(p[name + "_bytes"], p[name + "_tiled_bytes"])
     # refused: many tokens, many over a small W or a wide rank, other types, ranks not in fours
     for T, K, N, r, dt in ((129, 2048, 2048, 16, 0), (65, 1024, 1024, 16, 0), (33, 2048, 2048, 36, 0),
                            (24, 2048, 2048, 16, 1), (24, 2048, 2048, 6, 0), (24, 2048, 2048, 68, 0)):
-        assert lm.lora_few_token_plan(T, K, N, r, dt)["taken"] == 0, (T, K, N, r, dt)
+        p = lm.lora_few_token_plan(T, K, N, r, dt)
+        assert p["fwd_taken"] == p["bwd_taken"] == p["fwd_bytes"] == p["bwd_bytes"] == 0, (T, K, N, r, dt)
+    # more tiles than CUs: where the tiled kernels are the better ones, they stay
+    for T, K, N, r, want in ((96, 2048, 11008, 16, (0, 1)), (96, 2048, 11008, 0, (0, 1)), (96, 2048, 11008, 4, (1, 1)),
+                             (128, 8192, 3072, 4, (1, 0)), (128, 8192, 3072, 16, (1, 1)), (64, 3072, 8192, 32, (1, 1)),
+                             (96, 8192, 8192, 0, (0, 0)), (125, 8192, 16384, 20, (0, 1))):
+        p = lm.lora_few_token_plan(T, K, N, r)
+        assert (p["fwd_taken"], p["bwd_taken"]) == want, (T, K, N, r, p)
+        for op, name in ((lm.LORA_OP_FWD, "fwd"), (lm.LORA_OP_BWD, "bwd")):
+            n = lm.lora_linear_workspace_bytes(op, T, K, N, r, lm.LORA_BF16)
+            assert n == max(p[name + "_bytes"], p[name + "_tiled_bytes"])
     lib = lm.lib()
     plan = L._FewTokenPlan()
     assert lib.lora_few_token_plan(0, 128, 128, 8, 0, ctypes.byref(plan)) == EINVAL

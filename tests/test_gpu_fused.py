@@ -139,7 +139,7 @@ def test_backward_side_items_on_producers(orc, shape, recompute):
     d = {k: v.cuda() for k, v in inp.items()}
     assert lm.lora_linear_plan(T, K, N, r)["bwd_fused"]
     few = lm.lora_few_token_plan(T, K, N, r)  # (with the tiled kernels' workspace those run)
-    assert not few["taken"] or few["bwd_tiled_bytes"] < few["bwd_bytes"]
+    assert not few["bwd_taken"] or few["bwd_tiled_bytes"] < few["bwd_bytes"]
     ws = _ws(T, K, N, r)
     o = _buffers(T, K, N, r)
     _step(d, o, s, ws, ws[: few["bwd_tiled_bytes"]], recompute=recompute)

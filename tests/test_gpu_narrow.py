@@ -1,8 +1,8 @@
 """GPU tests of the few-token kernel (up to 128 tokens, bf16): tiles of 32 rows by
 64 columns, the reduction in one part or several that meet in the workspace, one
 or two blocks of 32 rank columns, one to four row tiles.  Each test asserts through
-lora_few_token_plan that its calls run that kernel (or, at the rule's edges and
-with the smaller workspace, the tiled ones).  Every result against the fp64 oracle
+lora_few_token_plan that its calls run that kernel (or, in one direction, at the
+rule's edges and with the smaller workspace, the tiled ones).  Every result against the fp64 oracle
 (max relative error <= 2e-2 per tensor, the bf16 bound of the other parity tests)."""
 import sys
 
@@ -31,27 +31,45 @@ SHAPES = [(1, 8, 8, 4), (1, 3072, 3072, 16), (16, 264, 72, 8), (24, 3072, 1032, 
           (32, 2056, 1032, 36), (20, 520, 2056, 40), (32, 1032, 264, 64), (17, 4104, 72, 64),
           (33, 776, 2056, 32), (64, 2048, 2048, 16), (50, 4104, 520, 24), (48, 520, 4104, 28),
           (65, 8200, 520, 24), (80, 1032, 4096, 12), (96, 4104, 1032, 16), (95, 520, 8200, 4),
-          (100, 4104, 1024, 32), (103, 1024, 4104, 16), (120, 2056, 2056, 0), (127, 2048, 2056, 16),
-          (128, 1032, 4104, 32), (128, 8200, 520, 8)]
+          (100, 4104, 1024, 32), (103, 1024, 4096, 16), (120, 2056, 2056, 0), (127, 2048, 2056, 16),
+          (128, 1040, 4096, 32), (128, 8200, 520, 8), (48, 264, 8200, 8)]
+# More tiles than CUs: one direction runs the few-token kernel, the other the tiled
+# ones (u in one sum or in partial sums of theirs; or u by the few-token kernel,
+# its reduction whole or in parts, ahead of a tiled backward); neither does.
+FWD_ONLY = [(100, 8200, 520, 4), (80, 8200, 1032, 12), (65, 8200, 2056, 4), (128, 8200, 520, 0)]
+BWD_ONLY = [(103, 1024, 4104, 16), (128, 520, 8200, 32), (48, 1032, 8200, 8), (100, 1032, 16384, 16), (100, 520, 8200, 0)]
 # The rule's edges: one token, one rank index or one weight row too many.
 BEYOND = [(129, 3072, 2056, 24), (65, 3080, 136, 8), (128, 64, 64, 8), (128, 2048, 2040, 16), (33, 776, 2056, 36),
-          (64, 256, 4104, 64), (100, 520, 3072, 40), (128, 2048, 3072, 64), (24, 1024, 520, 68), (24, 1024, 520, 6)]
+          (64, 256, 4104, 64), (100, 520, 3072, 40), (128, 2048, 3072, 64), (24, 1024, 520, 68), (24, 1024, 520, 6),
+          (65, 8200, 8200, 0)]
+
+
+def _taken(*shape):
+    p = lm.lora_few_token_plan(*shape)
+    return bool(p["fwd_taken"]), bool(p["bwd_taken"])
 
 
 def test_narrow_shapes_cover_the_plans():
+    for shapes, want in ((SHAPES, (True, True)), (FWD_ONLY, (True, False)), (BWD_ONLY, (False, True)),
+                         (BEYOND, (False, False))):
+        assert all(_taken(*s) == want for s in shapes), want
     plans = [lm.lora_few_token_plan(*s) | {"r": s[3]} for s in SHAPES]
-    assert all(p["taken"] for p in plans)
-    assert not any(lm.lora_few_token_plan(*s)["taken"] for s in BEYOND)
-    for parts in ("fwd_parts", "bwd_parts"):
+    for d in ("fwd", "bwd"):
+        parts, tiles_m = d + "_parts", d + "_tiles_m"
         for tiles in (1, 2, 3, 4):  # (row tiles) with the reduction whole and split
-            assert {p[parts] > 1 for p in plans if p["tiles_m"] == tiles and p["r"]} == {False, True}, (parts, tiles)
+            assert {p[parts] > 1 for p in plans if p[tiles_m] == tiles and p["r"]} == {False, True}, (d, tiles)
         assert any(p[parts] > 1 and p["r"] > 32 for p in plans) and any(p[parts] == 1 and p["r"] > 32 for p in plans)
+    assert {lm.lora_few_token_plan(*s)["fwd_parts"] > 1 for s in FWD_ONLY} == {False, True}
+    parts = {lm.lora_linear_plan(*s)["fwd_u_parts"] > 1 for s in BWD_ONLY if s[3]}
+    assert parts == {False, True}
 
 
-@pytest.mark.parametrize("shape", SHAPES + BEYOND, ids=["x".join(map(str, s)) for s in SHAPES + BEYOND])
+ALL = SHAPES + FWD_ONLY + BWD_ONLY + BEYOND
+
+
+@pytest.mark.parametrize("shape", ALL, ids=["x".join(map(str, s)) for s in ALL])
 def test_narrow_parity(orc, shape):
     T, K, N, r = shape
-    assert lm.lora_few_token_plan(*shape)["taken"] == (shape in SHAPES)
     _announce(f"narrow T={T} K={K} N={N} r={r}")
     inp = lora_inputs(T, K, N, r, seed=sum(shape))
     s = 2.0
@@ -75,7 +93,7 @@ def test_narrow_zero_B_is_rank_0(T, ranks):
     K, N = 2056, 2056
     _announce(f"narrow B=0 T={T}")
     for r in ranks:
-        assert lm.lora_few_token_plan(T, K, N, r)["taken"] and lm.lora_few_token_plan(T, K, N, 0)["taken"]
+        assert _taken(T, K, N, r)[0] and _taken(T, K, N, 0)[0]
         inp = lora_inputs(T, K, N, r, seed=T)
         inp["B"].zero_()
         d = {k: v.cuda() for k, v in inp.items()}
@@ -100,7 +118,7 @@ def test_narrow_workspace_contents_and_reuse(orc, fill):
         ws.fill_(fill)
     for it, (T, K, N, r) in enumerate([(24, 3072, 3072, 16), (120, 2048, 2056, 8), (24, 3072, 3072, 16)]):
         _announce(f"narrow workspace fill={fill} T={T}")
-        assert lm.lora_few_token_plan(T, K, N, r)["taken"]
+        assert _taken(T, K, N, r) == (True, True)
         inp = lora_inputs(T, K, N, r, seed=50 + it)
         d = {k: v.cuda() for k, v in inp.items()}
         o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
@@ -141,7 +159,7 @@ def test_narrow_graph_replay(orc):
     """Replays carry one tag: each must find the meetings' words as if new."""
     T, K, N, r = 123, 2048, 2056, 16
     s = 2.0
-    assert lm.lora_few_token_plan(T, K, N, r)["taken"]
+    assert _taken(T, K, N, r) == (True, True)
     d = {k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=60).items()}
     o = {"y": torch.empty(T, N, dtype=BF16, device="cuda"), "u": torch.empty(T, r, device="cuda"),
          "dx": torch.empty(T, K, dtype=BF16, device="cuda"), "dA": torch.empty(r, K, device="cuda"),
@@ -182,7 +200,7 @@ def test_narrow_replays_with_parts_and_row_tiles(shape):
     T, K, N, r = shape
     _announce(f"narrow replays T={T} K={K} N={N} r={r}")
     p = lm.lora_few_token_plan(T, K, N, r)
-    assert p["taken"] and p["bwd_parts"] > 1 and p["tiles_m"] > 1
+    assert p["bwd_taken"] and p["bwd_parts"] > 1 and p["bwd_tiles_m"] > 1
     inputs = [{k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=70 + i).items()} for i in range(3)]
     d = {k: torch.empty_like(v) for k, v in inputs[0].items()}
 
@@ -206,7 +224,7 @@ def test_narrow_replays_with_parts_and_row_tiles(shape):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         step(d, o, wf, wb)
-    tiles = p["tiles_m"] * p["bwd_tiles_n"]
+    tiles = p["bwd_tiles_m"] * p["bwd_tiles_n"]
     for it in range(30):
         for k in d:
             d[k].copy_(inputs[it % 3][k])
@@ -219,7 +237,7 @@ def test_narrow_replays_with_parts_and_row_tiles(shape):
         flags = wb.view(torch.int32)[: tiles * (p["bwd_parts"] + 1) * FLAG_WORDS]
         assert int(flags.count_nonzero()) == 0, it
         if p["fwd_parts"] > 1:
-            flags = wf.view(torch.int32)[: p["tiles_m"] * p["fwd_tiles_n"] * p["fwd_parts"] * FLAG_WORDS]
+            flags = wf.view(torch.int32)[: p["fwd_tiles_m"] * p["fwd_tiles_n"] * p["fwd_parts"] * FLAG_WORDS]
             assert int(flags.count_nonzero()) == 0, it
 
 
@@ -231,7 +249,7 @@ def test_narrow_over_data_of_other_calls(shape, fill):
     tokens.  Every result is that of a clean workspace, bitwise."""
     T, K, N, r = shape
     _announce(f"narrow over {fill} T={T}")
-    assert lm.lora_few_token_plan(T, K, N, r)["taken"]
+    assert _taken(T, K, N, r) == (True, True)
     many = {k: v.cuda() for k, v in lora_inputs(640, K, N, r, seed=80).items()}
     d = {k: v.cuda() for k, v in lora_inputs(T, K, N, r, seed=81).items()}
 
