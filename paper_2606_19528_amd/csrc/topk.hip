@@ -76,15 +76,18 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 // passes); every key at or above the prefix is then among the k best.  The
 // kept keys are written out wave by wave in a fixed order.
 //
-// A workgroup looks after SEL_ROWS rows: one load finds the counts of all of
+// A workgroup looks after up to SEL_ROWS rows: one load finds the counts of all of
 // them, and only the rows that need a selection cost more (a workgroup a row
-// spent 93 us on a pass over 128256 rows that selected nothing).
+// spent 93 us on a pass over 128256 rows that selected nothing).  Fewer rows a
+// workgroup as long as that leaves SEL_WGS workgroups or less, since the rows of
+// one follow one another: with 16 at every size the table of V = 1000 (D 256, k
+// 250) took 264 us instead of 65, of 4096 387 instead of 277.
 constexpr int SEL_Q = SEL_MAX / (4 * SEL_NT);  // vectors of 4 slots per thread
-constexpr int SEL_ROWS = 16;
+constexpr int SEL_ROWS = 16, SEL_WGS = 4096;
 static_assert(SEL_NT == 256, "one histogram bucket per thread");
 __global__ __launch_bounds__(SEL_NT) void topk_select_kernel(uint64_t *ckey, int *cnt, float *thr, int cap, int k,
                                                              int lazy, int final, int32_t *table, float *tvals,
-                                                             int64_t row0, int R) {
+                                                             int64_t row0, int R, int rows) {
   __shared__ uint64_t out[2048];  // final: the kept keys, sorted in place
   __shared__ int hist[2][256];
   __shared__ int wcount[SEL_NW];
@@ -92,8 +95,8 @@ __global__ __launch_bounds__(SEL_NT) void topk_select_kernel(uint64_t *ckey, int
   __shared__ uint64_t s_prefix;
   __shared__ int s_rank, s_done;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int first = blockIdx.x * SEL_ROWS;
-  const bool mine = lane < SEL_ROWS && first + lane < R;
+  const int first = blockIdx.x * rows;
+  const bool mine = lane < rows && first + lane < R;
   const int counts = mine ? min(cnt[first + lane], cap) : 0;
   // (not final: the others have room left for the next chunk)
   uint64_t todo = __ballot(mine && (final || counts > (lazy > k ? lazy : k)));
@@ -298,8 +301,9 @@ hipError_t launch_topk_reset(float *thr, int *cnt, int R, float lowest, hipStrea
 hipError_t launch_topk_select(const TopkArgs &a, int R, int final, hipStream_t st) {
   if (a.k > 2048 || a.k < 1 || a.cap < a.k || a.lazy > a.cap || a.cap > SEL_MAX || a.cap % 4)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(topk_select_kernel, dim3((R + SEL_ROWS - 1) / SEL_ROWS), dim3(SEL_NT), 0, st, a.key, a.cnt, a.thr,
-                     a.cap, a.k, a.lazy, final, a.table, a.tvals, a.row0, R);
+  const int rows = std::min(SEL_ROWS, std::max(1, R / SEL_WGS));
+  hipLaunchKernelGGL(topk_select_kernel, dim3((R + rows - 1) / rows), dim3(SEL_NT), 0, st, a.key, a.cnt, a.thr, a.cap,
+                     a.k, a.lazy, final, a.table, a.tvals, a.row0, R, rows);
   return hipGetLastError();
 }
 
