@@ -148,7 +148,8 @@ lora_status_t frozen_linear_bwd_dx(const void *dy, const void *W, void *dx, int6
                                    size_t ws_bytes, void *hip_stream);
 /* Workspace with which frozen_linear_bwd_dx (and its quantized form) splits a
  * long reduction over CUs that the output's tiles would leave idle; 0 where
- * that does not pay, (size_t)-1 for rejected sizes; at most 64 MiB.  Optional:
+ * that does not pay, (size_t)-1 for rejected sizes; at most 64 MiB (a bf16 call
+ * may leave it unused where only the quantized form gains).  Optional:
  * with less, or none, the call runs unsplit, which sums in another order (the
  * results then differ by the rounding of fp32 sums). */
 size_t frozen_linear_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt);

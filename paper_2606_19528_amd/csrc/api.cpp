@@ -784,8 +784,8 @@ lora_status_t bwd_impl(const void *x, const void *W, const void *qc, const float
   return LORA_OK;
 }
 
-size_t frozen_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt) {
-  const int n = dt == LORA_BF16 ? gemm_splits(T, d_in, d_out) : 1;
+size_t frozen_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt, bool quant) {
+  const int n = dt == LORA_BF16 ? gemm_splits(T, d_in, d_out, quant) : 1;
   return n > 1 ? (size_t)n * T * d_in * 4 : 0;
 }
 
@@ -827,7 +827,7 @@ lora_status_t frozen_impl(const void *dy, const void *W, const void *qc, const f
   set_qweight(g, qc ? &qw : nullptr);
   // The workspace is optional here: with room for the planes of a split
   // reduction (and clear of the operands) the split one runs.
-  const size_t planes = frozen_split_bytes(T, d_in, d_out, dt);
+  const size_t planes = frozen_split_bytes(T, d_in, d_out, dt, qc != nullptr);
   const Range wr = rng(ws, (int64_t)planes);
   const bool split = planes > 0 && ws && ws_bytes >= planes && aligned16(ws) && !any_overlap({wr, outs[0]}, ins) &&
                      (!qc || (qw.log2g >= 6 && gemm_q_direct(g, bits, true, false)));
@@ -903,7 +903,7 @@ lora_status_t frozen_linear_bwd_dx(const void *dy, const void *W, void *dx, int6
 
 size_t frozen_linear_split_bytes(int64_t T, int64_t d_in, int64_t d_out, lora_dtype_t dt) {
   if (check_shapes(T, d_in, d_out, 0, dt) != LORA_OK) return (size_t)-1;
-  return frozen_split_bytes(T, d_in, d_out, dt);
+  return frozen_split_bytes(T, d_in, d_out, dt, true);  // (a split bf16 product is split quantized too)
 }
 
 lora_status_t frozen_linear_bwd_dx_q(const void *dy, const void *W_codes, const float *W_scale,

@@ -166,13 +166,13 @@ __global__ __launch_bounds__(256) void sum_planes_kernel(const float *planes, in
   }
 }
 
-int gemm_splits(int64_t M, int64_t N, int64_t K) {
+int gemm_splits(int64_t M, int64_t N, int64_t K, bool quant) {
   int chunk;
-  return split_plan(M, N, K, &chunk);
+  return split_plan(M, N, K, quant, &chunk);
 }
 
 hipError_t launch_gemm_split(GemmArgs g, int bits, float *planes, hipStream_t st) {
-  const int np = split_plan(g.M, g.N, g.K, &g.k_chunk);
+  const int np = split_plan(g.M, g.N, g.K, bits != 16, &g.k_chunk);
   uint16_t *C = (uint16_t *)g.C;
   if (np < 2 || g.r != 0 || g.ldc != g.N || g.N % 8) return hipErrorInvalidValue;
   g.C = planes;

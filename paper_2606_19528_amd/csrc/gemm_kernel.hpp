@@ -2041,10 +2041,16 @@ static inline int pick_shape(int M, int N, bool b_kmajor, bool with_side) {
 // ranges of k as fill the 256 CUs once, each of at least 1024 k-rows, at most
 // 32.  Costs as in pick_shape, times the k-rows, in units of a full-rate CU's
 // products; writing and reading the planes (8 bytes per element, about 4
-// TB/s) is 4.4 such units per element.  Measured at 1024 x 3072 over 128256:
-// 192 tiles of 128 x 128 unsplit 1124 us, 48 tiles of 256 x 256 x 5 ranges
-// 672 us.  Returns the number of ranges (1: no split) and the k-rows of each.
-static inline int split_plan(int64_t M, int64_t N, int64_t K, int *k_chunk) {
+// TB/s) is 4.4 such units per element.  2.4 M units take a CU about 1 us.  A split
+// bf16 product was measured at 3 us (the second launch) and 0.9 of its units, an
+// unsplit one at 0.8 of them, or on 128 x 64 tiles, which run faster few at a time,
+// at 3.5 us and 0.6; of 247 random shapes 243 then split, at 0.05 - 1.09 of the
+// unsplit time (the other four lost up to half: 218 x 256 over 4096 18.6 -> 27.9
+// us).  Dequantizing tiles gain from 0.9 of the units on (250 shapes, 0.06 - 0.85).
+// Measured at 1024 x 3072 over 128256: 192 tiles of 128 x 128 unsplit 1124 us, 48
+// tiles of 256 x 256 x 5 ranges 672 us.  Returns the number of ranges (1: no
+// split) and the k-rows of each.
+static inline int split_plan(int64_t M, int64_t N, int64_t K, bool quant, int *k_chunk) {
   const int64_t b = M <= 128 ? 128 : 256;
   const int64_t tiles = ((M + b - 1) / b) * ((N + b - 1) / b);
   const int64_t n = std::min<int64_t>({tiles > 128 ? 1 : 256 / tiles, K / 1024, 32});
@@ -2055,7 +2061,8 @@ static inline int split_plan(int64_t M, int64_t N, int64_t K, int *k_chunk) {
   const int c = pick_shape((int)M, (int)N, true, false);
   const double whole = tile_cost(M, N, shp[c][0], shp[c][1], kEffKmaj[c]) * (double)K;
   const double split = (double)b * b / kEffKmaj[b == 128 ? 0 : 2] * (double)chunk + 4.4 * (double)(M * N * np);
-  if (split > 0.9 * whole) return 1;
+  constexpr double us = 2.4e6;
+  if (quant ? split > 0.9 * whole : 3 * us + 0.9 * split > (c == 3 ? 3.5 * us + 0.6 * whole : 0.8 * whole)) return 1;
   *k_chunk = (int)chunk;
   return (int)np;
 }

@@ -201,7 +201,7 @@ hipError_t launch_gemm(const GemmArgs &g, Dtype dt, bool b_kmajor, const SideArg
 // (1: it does not pay), and the product itself (bits 16: bf16 B, else
 // quantized): C bf16 = sum over the ranges, in ascending order, of their fp32
 // planes [ranges][M][N] at `planes`.
-int gemm_splits(int64_t M, int64_t N, int64_t K);
+int gemm_splits(int64_t M, int64_t N, int64_t K, bool quant);
 hipError_t launch_gemm_split(GemmArgs g, int bits, float *planes, hipStream_t st);
 hipError_t launch_gemm_split_q(const GemmArgs &g, int bits, int splits, hipStream_t st);
 

@@ -41,6 +41,7 @@ def test_frozen_dx_split(T, d_in, d_out):
     assert n >= 2 * T * d_in * 4
     ws = torch.full((n + 256,), 0xFF, dtype=torch.uint8, device="cuda")  # NaN planes unless written
     dx = lm.frozen_linear_bwd_dx(dy, W, torch.empty(T, d_in, dtype=torch.bfloat16, device="cuda"), ws=ws[:n])
+    assert not bool((ws[: T * d_in * 4] == 0xFF).all())  # (the first plane is written: it split)
     again = lm.frozen_linear_bwd_dx(dy, W, torch.empty_like(dx))
     small = lm.frozen_linear_bwd_dx(dy, W, torch.empty_like(dx), ws=ws[: n - 16])  # no room: unsplit
     torch.cuda.synchronize()
@@ -119,3 +120,18 @@ def test_no_room_for_the_optional_workspaces():
     _check(split, dy, W)
     _check(unsplit, dy, W)
     assert torch.equal(tables[0], tables[1])
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [(130, 1024, 4096), (218, 256, 4096), (2683, 1024, 8576)])
+def test_short_reductions_stay_whole(T, d_in, d_out):
+    """Where the second launch costs more than the split gains, a bf16 product leaves
+    the workspace alone."""
+    _announce(f"frozen whole T={T} {d_out}->{d_in}")
+    g = torch.Generator().manual_seed(T)
+    dy = torch.randn(T, d_out, generator=g).bfloat16().cuda()
+    W = (torch.randn(d_out, d_in, generator=g) * 0.02).bfloat16().cuda()
+    ws = torch.full((max(_split_bytes(T, d_in, d_out), 1 << 20),), 0xFF, dtype=torch.uint8, device="cuda")
+    dx = lm.frozen_linear_bwd_dx(dy, W, torch.empty(T, d_in, dtype=torch.bfloat16, device="cuda"), ws=ws)
+    torch.cuda.synchronize()
+    assert bool((ws == 0xFF).all())
+    _check(dx, dy, W)
