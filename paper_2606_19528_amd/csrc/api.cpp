@@ -144,7 +144,7 @@ bool fuse_ok(int64_t T, int64_t N, int64_t K, int64_t r, lora_dtype_t dt, bool b
 }
 // Tag of a fused launch: distinct for every call of this process, never 0.
 unsigned int next_gen() {
-  static std::atomic<unsigned int> g{0};
+  static std::atomic<unsigned int> g{(unsigned int)random_word()};  // (no small number that data may hold)
   unsigned int v;
   do {
     v = ++g;
@@ -254,9 +254,9 @@ BwdLayout bwd_layout(int64_t T, int64_t K, int64_t N, int64_t r, lora_dtype_t dt
 //     hand-over is most of the time (0.7 - 0.93); else it loses (1.0 - 2.0: 96
 //     tokens of 2048 -> 11008 at r = 16 21.2 against 16.0 us), as at rank 0;
 //   forward, unfused: ranks that are not multiples of 8, which the tiled kernels
-//     pad (0.05 - 1.0), up to 96 tokens or a tile count times d_in of 5 M (beyond 0.9 - 1.4);
-//     other ranks (wide outputs) up to half of that and 64 tokens, or 96 over 1024
-//     columns of x (0.6 - 0.9, beyond 1.0 - 1.6);
+//     pad (0.05 - 1.0), up to 96 tokens or a tile count times d_in of 5 M (beyond
+//     0.9 - 1.4); other ranks (wide outputs) up to half of that product and 64
+//     tokens, or 96 over 1024 columns of x (0.6 - 0.9, beyond 1.0 - 1.6);
 //   backward, fused, where few producers run the dA / dB items: always (0.1 - 0.9);
 //   backward, unfused: ranks that are not multiples of 8 up to 64 tokens or 320
 //     tiles (0.6 - 1.04), and at r >= 20 over 2048 rows of W (0.6 - 1.1); else it

@@ -28,10 +28,18 @@ namespace lora {
 
 using meet_word = uint64_t;
 
+// A number of the system's random source.
+inline uint64_t random_word() {
+  uint64_t v = 0;
+  if (getentropy(&v, sizeof v) == 0) return v;
+  // (no random source: the time in ns, spread over the word by an odd factor)
+  return (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull;
+}
+
 // Tags of a process's launches, never 0 and never the same twice (2^52 of them).
 class MeetTags {
  public:
-  MeetTags() : next_(start()) {}
+  MeetTags() : next_(random_word()) {}
   meet_word take() {
     uint64_t payload;
     do {
@@ -42,12 +50,6 @@ class MeetTags {
 
  private:
   static constexpr uint64_t BITS = uint64_t(1) << 52;
-  static uint64_t start() {
-    uint64_t v = 0;
-    if (getentropy(&v, sizeof v) == 0) return v;
-    // (no random source: the time in ns, spread over the word by an odd factor)
-    return (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull;
-  }
   std::atomic<uint64_t> next_;
 };
 
