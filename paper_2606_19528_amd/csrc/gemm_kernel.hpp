@@ -1203,16 +1203,19 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
       for (int s2 = 0; s2 < SPW; ++s2) read_frags_d(BUF, s2, f[s2]);
     };
     auto mma_stage = [&](const Frag(&f)[SPW]) {
+      if constexpr (DUAL) {
+        // (the second fragment set holds the odd stages)
+        auto &sums = &f == &F[1] ? acc2 : acc;
+#pragma unroll
+        for (int s2 = 0; s2 < SPW; ++s2)
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) mma32(E(), sums[i][j], f[s2].b[j], f[s2].a[i]);
+        return;
+      }
 #pragma unroll
       for (int s2 = 0; s2 < SPW; ++s2) mma_frags(f[s2]);
-    };
-    auto mma_stage2 = [&](const Frag(&f)[SPW]) {  // into acc2
-#pragma unroll
-      for (int s2 = 0; s2 < SPW; ++s2)
-#pragma unroll
-        for (int i = 0; i < (DUAL ? FM : 0); ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) mma32(E(), acc2[i][j], f[s2].b[j], f[s2].a[i]);
     };
     if constexpr (QD) {
       // Quantized B.  Step kt: wait for its loads of stage kt + 1 and of the
@@ -1342,8 +1345,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(GemmArgs g, int
           static_for<ri * IPS / NRO, (ri + 1) * IPS / NRO>(
               [&](auto QI) { dma_one(IC<P % NBUF>(), kt + NBUF, QI, MASK); });
         });
-        if constexpr (DUAL && P % 2) mma_stage2(F[P % 2]);
-        else mma_stage(F[P % 2]);
+        mma_stage(F[P % 2]);
         constexpr int NM = SPW * FM * FN;
         constexpr int NR = SPW * (FM + FN * (BMODE == B_KMAJ_TR ? 2 : 1));
         static_for<0, NM>([&](auto MI) {
